@@ -19,16 +19,23 @@ LIB = os.path.join(HERE, "libsla.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["api.cpp", "commit.hip", "conv.hip", "decode.hip", "draft.hip", "verify_serial.hip", "verify_tile.hip"]
+# (source, object name, definitions); the tile kernel first, it takes longest
+SOURCES = [("verify_tile.hip", "verify_tile_%d_%s_%s" % (dk, form, dt),
+            ["-DSLA_TILE_DK=%d" % dk, "-DSLA_TILE_GATES=%d" % (form == "gates"), "-DSLA_TILE_F32=%d" % (dt == "f32")])
+           for dk in (128, 256, 64) for form in ("scalar", "gates") for dt in ("bf16", "f32")]
+SOURCES += [(src, os.path.splitext(src)[0], []) for src in
+            ("api.cpp", "commit.hip", "conv.hip", "decode.hip", "draft.hip", "verify_serial.hip",
+             "verify_tile_dispatch.cpp")]
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH, "-I" + INCLUDE, "-I" + CSRC,
           "-Wall", "-Wno-unused-result",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
-def _compile(src: str, verbose: bool) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
+def _compile(unit, verbose: bool) -> str:
+    src, name, defines = unit
+    obj = os.path.join(BUILD, name + ".o")
     lang = ["-x", "hip"] if src.endswith(".hip") else []
-    cmd = [HIPCC] + COMMON + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC] + COMMON + defines + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -72,6 +72,10 @@ hipError_t launch_verify_serial(const VerifyArgs &a, int dtype, hipStream_t s);
 hipError_t launch_verify_hybrid(const VerifyArgs &a, int dtype, hipStream_t s);
 bool parallel_supported(int dk, int dv, int n, int dtype);
 hipError_t launch_verify_parallel(const VerifyArgs &a, int dtype, hipStream_t s);
+// the contraction for one head size, scalar or per-key gates, activation type
+// (specialised in the units of verify_tile.hip)
+template <int DK, bool GATES, bool F32>
+hipError_t launch_tile(const VerifyArgs &a, hipStream_t s);
 // 1-node drafts (a.n == 1), any family and activation dtype
 hipError_t launch_verify_decode(const VerifyArgs &a, int dtype, hipStream_t s);
 hipError_t launch_commit(const CommitArgs &a, int dtype, hipStream_t s);

@@ -14,8 +14,9 @@
 // T_tree = solve_tril(I - A_tree), and O = Q^ S0^T - Attn W S0^T + Attn U.
 // Both per-column products run on the matrix cores:
 //     U = T R,      O = Gamma P_q + Attn U,
-// and the only sequential work is the small per-unit T (each lane walks its
-// own node's root path).  Only the committed state is read.
+// the first as a substitution over 16-row blocks (only the diagonal blocks
+// of T are formed), and the only sequential work is the small per-unit
+// inverse of those blocks.  Only the committed state is read.
 //
 // One workgroup = one (batch b, head h) unit's V-tile of CW x 16 columns
 // (CW = 4 or 8), or TPW = 2 consecutive such tiles, with CW + 1 wavefronts
@@ -47,8 +48,8 @@
 //              16-node tiles with scalar gates, the second tile's first d_k/2
 //              state rows, which would otherwise queue behind the first
 //              tile's work (measured at batch 64, 16 heads, d_v 128: 37.8 ->
-//              36.9 us per launch).  After the Grams it solves the per-node
-//              rows of T.
+//              36.9 us per launch).  After the Grams it inverts the diagonal
+//              blocks of T.
 // The tree-masked Grams ([Q; K] K^T tiles that hold ancestor pairs, exact
 // bf16 products) run on the column waves; they and T are done while the
 // first tile's state is still in flight.  Strided global accesses go through
@@ -69,7 +70,6 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 constexpr int kWaveCols = 16;                    // state columns per column wave
 constexpr int kPMax = 8;                          // pending steps staged in LDS
 constexpr int kBP = 20;                           // fp32 row pitch of a 16x16 block
-constexpr int kZ = 8;                             // root paths up to this depth solve T in registers
 
 // Layer families by the form of their step (template parameter KIND):
 //   kKindDelta  scalar gates: GDN, DeltaNet (alpha = 1) and the scalar decay
@@ -95,13 +95,11 @@ struct Layout {
   static constexpr int ES = F32 ? 4 : 2;            // bytes per activation
   static constexpr int NT = NP / 16, KS = DK / 32, CH = DK * ES / 16, MT = 2 * NT;
   static constexpr int NB = NT * (NT + 1) / 2;      // lower-triangular 16x16 blocks
-  static constexpr int kList = NP * (NP + 1) / 2;   // compact Lk capacity (floats)
   static constexpr bool kDelta = KIND == kKindDelta, kGates = KIND == kKindGates;
   static constexpr int kX = 2 * NP * CH * 16;       // [Q; K], 16-byte chunks, xor-swizzled
   static constexpr int kBlk = 16 * kBP * 4;
-  static constexpr int kT = kDelta ? NB * kBlk : 0;   // T blocks
+  static constexpr int kT = kDelta ? NB * kBlk : 0;   // -Lk blocks, the diagonal ones inverted in place
   static constexpr int kAt = NB * kBlk;             // Attn blocks
-  static constexpr int kLk = kDelta ? kList * 4 : 0;
   static constexpr int kPk = kPMax * DK * ES;       // pending keys (activation dtype)
   static constexpr int kPu = TPW * kPMax * kTileCols * 4;  // pending corrected values, one stage per tile
   static constexpr int kXL = (kGates && !F32) ? kX / 2 : 0;  // low halves of Q~, same chunk layout
@@ -115,8 +113,8 @@ struct Layout {
   static constexpr bool kPrefetch = TPW == 2 && NP == 16 && CW == 4 && kDelta;
   static constexpr int kPreInstr = kPrefetch ? (DK / 2) * (kTileCols / 4) / kWave : 0;  // 16-byte loads per lane
   static constexpr int kPre = kPreInstr * kWave * 16;
-  static constexpr int kTopo = NP * 8 + NP * 4 * 4 + kPMax * 4 + 16;
-  static constexpr int oT = kX, oAt = oT + kT, oLk = oAt + kAt, oPk = oLk + kLk, oPu = oPk + kPk;
+  static constexpr int kTopo = NP * 8 + NP * 2 * 4 + kPMax * 4 + 16;
+  static constexpr int oT = kX, oAt = oT + kT, oPk = oAt + kAt, oPu = oPk + kPk;
   static constexpr int oXL = oPu + kPu, oG = oXL + kXL, oPg = oG + kG, oPre = oPg + kPg, oTopo = oPre + kPre;
   static constexpr int kBytes = oTopo + kTopo;
 };
@@ -204,9 +202,8 @@ void verify_tile_kernel(VerifyArgs a) {
 
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   uint4 *xs = reinterpret_cast<uint4 *>(lds);                 // [Q; K] (GLA: high halves of Q~ in place of Q)
-  float *tb = reinterpret_cast<float *>(lds + L::oT);         // T blocks
+  float *tb = reinterpret_cast<float *>(lds + L::oT);         // -Lk blocks; diagonal ones become N = T - I
   float *ab = reinterpret_cast<float *>(lds + L::oAt);        // Attn blocks
-  float *lk = reinterpret_cast<float *>(lds + L::oLk);        // compact Lk
   AT *s_pk = reinterpret_cast<AT *>(lds + L::oPk);            // [kPMax][DK]
   float *s_pu = reinterpret_cast<float *>(lds + L::oPu);      // [kPMax][64]
   uint4 *xl = reinterpret_cast<uint4 *>(lds + L::oXL);        // GLA: low halves of Q~
@@ -215,15 +212,13 @@ void verify_tile_kernel(VerifyArgs a) {
   float *s_pre = reinterpret_cast<float *>(lds + L::oPre);    // second tile's first DK/2 state rows
   unsigned char *tp = lds + L::oTopo;
   uint64_t *s_anc = reinterpret_cast<uint64_t *>(tp);      // [NP]
-  int *s_depth = reinterpret_cast<int *>(tp + 8 * NP);     // [NP]
-  int *s_off = s_depth + NP;                                // [NP]
-  float *s_gamma = reinterpret_cast<float *>(s_off + NP);  // [NP]
+  float *s_gamma = reinterpret_cast<float *>(tp + 8 * NP);  // [NP]
   float *s_be = s_gamma + NP;                               // [NP]
   float *s_palpha = s_be + NP;                              // [kPMax]
   int *s_misc = reinterpret_cast<int *>(s_palpha + kPMax);  // err, path len
 
   const int tid = threadIdx.x;
-  const int w = tid / kWave;
+  const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int l = tid % kWave;
   const int lc = l & 15;  // column within a wave's 16 / row within a 16-row tile
   const int lg = l >> 4;  // row group
@@ -345,42 +340,63 @@ void verify_tile_kernel(VerifyArgs a) {
     if (a.chain) bad = bad || (live && p != l - 1);
     int err = wave_any(bad) ? SLA_ERR_TOPOLOGY : SLA_OK;
     if (err == SLA_OK) {
-      // Walking up from j, g holds D_jx = product of the gates of P(j)
-      // strictly below x (j included) when the walk reaches ancestor x; the
-      // scalar families park it in the (not yet used) T block at (j, x) for
-      // the Grams.  Only products of gates: they may underflow, never
-      // overflow (no reciprocal of a decay product anywhere).
+      // Root paths.  p_s is a node's s-th ancestor (-1 past the root) and g_s
+      // the product of the gates of its first s path nodes, itself included:
+      // D_jx = g_s for the ancestor x = p_s.  Four walkers per lane start at
+      // ancestors 1 to 4 and hop four at a time (their lane reads are
+      // independent, so a round costs about one of them); the scalar families
+      // park each D_jx at (j, x) of the Attn and the Lk blocks for the Grams.
+      // Products of gates only: they may underflow, never overflow (no
+      // reciprocal of a decay product anywhere).  One hop per ancestor took
+      // 10 us of a 48-node chain's launch.
       uint64_t m = live ? (1ull << l) : 0ull;
-      float g = al;
-      int d = live ? 1 : 0;
-      int x = p;
-      if (DELTA && live) tb[blk(l, l)] = 1.f;
-      while (wave_any(x >= 0)) {
-        const int src = x >= 0 ? x : 0;
-        const float ax = __shfl(al, src);
-        const int px = __shfl(p, src);
-        if (x >= 0) {
-          if constexpr (DELTA) tb[blk(l, x)] = g;
-          m |= 1ull << x;
-          g *= ax;
-          ++d;
+      auto up = [](int x, int v) { return __shfl(v, x >= 0 ? x : 0); };
+      auto upf = [](int x, float v) { return __shfl(v, x >= 0 ? x : 0); };
+      int xw[4];
+      float gw[4];
+      xw[0] = p;
+      gw[0] = al;
+      {
+        const int pa = up(p, p);
+        const float ga = upf(p, al);
+        xw[1] = p >= 0 ? pa : -1;
+        gw[1] = p >= 0 ? al * ga : al;
+        const int pb = up(xw[1], p), pc = up(xw[1], xw[1]);
+        const float gb = upf(xw[1], al), gc = upf(xw[1], gw[1]);
+        xw[2] = xw[1] >= 0 ? pb : -1;
+        gw[2] = xw[1] >= 0 ? gw[1] * gb : gw[1];
+        xw[3] = xw[1] >= 0 ? pc : -1;
+        gw[3] = xw[1] >= 0 ? gw[1] * gc : gw[1];
+      }
+      const int p4 = xw[3];
+      const float g4 = gw[3];
+      if (DELTA && live) ab[blk(l, l)] = 1.f;
+      while (wave_any(xw[0] >= 0)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int x = xw[r];
+          const int px = up(x, p4);
+          const float gx = upf(x, g4);
+          if (x >= 0) {
+            if constexpr (DELTA) {
+              ab[blk(l, x)] = gw[r];
+              tb[blk(l, x)] = gw[r];
+            }
+            m |= 1ull << x;
+            gw[r] *= gx;  // walker 0, once past the root: the gates of the whole path
+            xw[r] = px;
+          }
         }
-        x = x >= 0 ? px : -1;
       }
-      int incl = d;  // inclusive prefix sum of depths -> compact-list offsets
+      const int d = __popcll(m);
+      if constexpr (GV) {  // the deepest root path
+        maxd = d;
 #pragma unroll
-      for (int o = 1; o < kWave; o <<= 1) {
-        const int y = __shfl_up(incl, o);
-        if (l >= o) incl += y;
+        for (int o = 1; o < kWave; o <<= 1) maxd = max(maxd, __shfl_xor(maxd, o));
       }
-      maxd = d;
-#pragma unroll
-      for (int o = 1; o < kWave; o <<= 1) maxd = max(maxd, __shfl_xor(maxd, o));
       if (live) {
         s_anc[l] = m;
-        s_depth[l] = d;
-        s_off[l] = incl - d;
-        s_gamma[l] = g;
+        s_gamma[l] = gw[0];
         s_be[l] = be;
       }
     }
@@ -651,28 +667,21 @@ void verify_tile_kernel(VerifyArgs a) {
         const int an = na * 16 + lc;
         const int jb = (mr % NT) * 16 + 4 * lg;
         uint32_t anc[4];  // the half of row j's ancestor mask that holds column an
-        float dj[4], bj[4];  // dj: decay ratio D_{j,an}, parked in the T block (j, an)
-        int oj[4];
+        float dj[4], bj[4];  // dj: decay ratio D_{j,an}, parked where the entry goes
+        float *const db = mr < NT ? ab : tb;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           anc[q] = reinterpret_cast<const uint32_t *>(s_anc)[2 * (jb + q) + (na >> 1)];
-          dj[q] = tb[blk(jb + q, an)];  // an <= 16 (jb / 16) + 15: inside the block row
-          if (mr >= NT) {
-            bj[q] = s_be[jb + q];
-            oj[q] = s_off[jb + q];
-          }
+          dj[q] = db[blk(jb + q, an)];  // an <= 16 (jb / 16) + 15: inside the block row
+          if (mr >= NT) bj[q] = s_be[jb + q];
         }
-        const int da = mr >= NT ? s_depth[an] : 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int j = jb + q;
           // rows past the last node hold stale LDS words: masked by j < n
           if (j >= n || an > j || (mr >= NT && an == j) || !((anc[q] >> (an & 31)) & 1u)) continue;
           const float dg = dj[q] * gacc[tc / kColWaves][q];
-          if (mr < NT)
-            ab[blk(j, an)] = dg;
-          else
-            lk[oj[q] + da - 1] = bj[q] * dg;
+          db[blk(j, an)] = mr < NT ? dg : -(bj[q] * dg);
         }
       }
   }
@@ -681,62 +690,33 @@ void verify_tile_kernel(VerifyArgs a) {
   __syncthreads();
 
   if (DELTA && w == kSetup) {
-    // ---- T = (I + Lk)^-1, one lane per row j.  With p_0 .. p_{d-1} = j the
-    //      root path of j and x_t = T_{j p_t}:  x_{d-1} = 1,
-    //      x_t = - sum_{u > t} x_u Lk_{p_u p_t}.
-    if (l < n) {
-      const int j = l;
-      const uint64_t m = s_anc[j];
-      tb[blk(j, j)] = 1.f;
-      if (maxd <= kZ) {
-        // push form, deepest node first: once x_u is known its terms go to
-        // every shallower position; z[k] accumulates position u - 1 - k, so
-        // the next unknown is always z[0] (registers, no LDS round trip per
-        // term; the Lk reads of one node are independent and go out together)
-        const int d = s_depth[j];
-        float z[kZ];
+    // ---- the diagonal blocks of T = (I + Lk)^-1, less the identity, in place
+    //      (the off-diagonal blocks stay -Lk: U = T R is a substitution block
+    //      row by block row).  Lane (nb, c) solves column c of block nb by
+    //      forward substitution in registers; the cost does not depend on the
+    //      depth of the tree (one lane per row, walking its root path, took
+    //      1.6 us at depth 8, 12 us on a 16-node chain and 107 us on a 48-node
+    //      chain, on the critical path of a single sequence).
+    const int nb = l >> 4, c = l & 15;
+    if (nb < NT) {
+      float *const db = tb + ((nb * (nb + 1)) / 2 + nb) * (16 * kBP);
+      float x[16];
+      x[0] = c == 0 ? 1.f : 0.f;
 #pragma unroll
-        for (int k = 0; k < kZ; ++k) z[k] = 0.f;
-        uint64_t rest = m & ~(1ull << j);
-        float xu = 1.f;
-        int pu = j;
-        for (int u = d - 1; u >= 1; --u) {
-          const float *lrow = lk + s_off[pu];
+      for (int j = 1; j < 16; ++j) {
+        float sum = j == c ? 1.f : 0.f;
 #pragma unroll
-          for (int k0 = 0; k0 < kZ; k0 += 8) {  // eight reads per round trip
-            float lv[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) lv[k] = (u - 1 - k0 - k >= 0) ? lrow[u - 1 - k0 - k] : 0.f;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) z[k0 + k] = __builtin_fmaf(xu, lv[k], z[k0 + k]);
-          }
-          const int pn = 63 - __builtin_clzll(rest);  // p_{u-1}: deepest ancestor left
-          rest &= ~(1ull << pn);
-          xu = -z[0];
-          tb[blk(j, pn)] = xu;
-#pragma unroll
-          for (int k = 0; k + 1 < kZ; ++k) z[k] = z[k + 1];
-          z[kZ - 1] = 0.f;
-          pu = pn;
+        for (int a0 = 0; a0 < j; a0 += 4) {
+          const float4 lv = *reinterpret_cast<const float4 *>(db + j * kBP + a0);
+          sum = __builtin_fmaf(lv.x, x[a0], sum);
+          if (a0 + 1 < j) sum = __builtin_fmaf(lv.y, x[a0 + 1], sum);
+          if (a0 + 2 < j) sum = __builtin_fmaf(lv.z, x[a0 + 2], sum);
+          if (a0 + 3 < j) sum = __builtin_fmaf(lv.w, x[a0 + 3], sum);
         }
-      } else {
-        // pull form for deep paths, deepest ancestor first:
-        //   T_ja = - sum_{e in P(j), a < e} T_je Lk_ea
-        uint64_t rest = m & ~(1ull << j);
-        while (rest) {
-          const int an = 63 - __builtin_clzll(rest);
-          rest &= ~(1ull << an);
-          const int ta = s_depth[an] - 1;
-          uint64_t below = m & ~((2ull << an) - 1ull);
-          float sum = 0.f;
-          while (below) {
-            const int e = __builtin_ctzll(below);
-            below &= below - 1ull;
-            sum = __builtin_fmaf(-tb[blk(j, e)], lk[s_off[e] + ta], sum);
-          }
-          tb[blk(j, an)] = sum;
-        }
+        x[j] = sum;
       }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) db[j * kBP + c] = j == c ? 0.f : x[j];
     }
   }
 
@@ -844,6 +824,7 @@ void verify_tile_kernel(VerifyArgs a) {
       f32x4 pk[NT];
 #pragma unroll
       for (int mt = 0; mt < NT; ++mt) pk[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      bf16x8 bhi[F32 ? 1 : KS], blo[F32 ? 1 : KS];  // the state's two bf16 parts, in place of its registers
       if constexpr (DELTA && F32) {  // exact fp32 products: the state registers are the B operands
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
@@ -857,13 +838,12 @@ void verify_tile_kernel(VerifyArgs a) {
       } else if constexpr (DELTA) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-          bf16x8 bhi, blo;
-          split8(hf[ks], bhi, blo);
+          split8(hf[ks], bhi[ks], blo[ks]);
 #pragma unroll
           for (int mt = 0; mt < NT; ++mt) {
             const bf16x8 af = *reinterpret_cast<const bf16x8 *>(xs + xchunk<CH>(NP + mt * 16 + lc, ks * 4 + lg));
-            pk[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bhi, pk[mt], 0, 0, 0);
-            pk[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, blo, pk[mt], 0, 0, 0);
+            pk[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bhi[ks], pk[mt], 0, 0, 0);
+            pk[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, blo[ks], pk[mt], 0, 0, 0);
           }
         }
       }
@@ -895,16 +875,15 @@ void verify_tile_kernel(VerifyArgs a) {
       } else {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-          bf16x8 bhi, blo;
-          split8(hf[ks], bhi, blo);
+          if constexpr (!DELTA) split8(hf[ks], bhi[ks], blo[ks]);
 #pragma unroll
           for (int mt = 0; mt < NT; ++mt) {
             const bf16x8 af = *reinterpret_cast<const bf16x8 *>(xs + xchunk<CH>(mt * 16 + lc, ks * 4 + lg));
-            pq[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bhi, pq[mt], 0, 0, 0);
-            pq[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, blo, pq[mt], 0, 0, 0);
+            pq[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bhi[ks], pq[mt], 0, 0, 0);
+            pq[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, blo[ks], pq[mt], 0, 0, 0);
             if constexpr (GV) {  // Q~ lo half
               const bf16x8 afl = *reinterpret_cast<const bf16x8 *>(xl + xchunk<CH>(mt * 16 + lc, ks * 4 + lg));
-              pq[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afl, bhi, pq[mt], 0, 0, 0);
+              pq[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afl, bhi[ks], pq[mt], 0, 0, 0);
             }
           }
         }
@@ -948,43 +927,41 @@ void verify_tile_kernel(VerifyArgs a) {
     }
     if (cols_live) {  // no early return: every wave takes every later barrier
       // ---- U = T R, then O = Gamma P_q + Attn U, on the matrix cores; A
-      //      fragments are rows j = 16 mt + lc, columns 16 ks + 4 lg .. + 3
+      //      fragments are rows j = 16 mt + lc, columns 16 ks + 4 lg .. + 3.
+      //      U by block rows: X = R - sum over the blocks to the left of
+      //      Lk U, then U = X + (T - I) X with the diagonal block's T: R
+      //      enters the fp32 accumulators as it is
       f32x4 uacc[NT];  // same layout as R
-      if constexpr (DELTA && F32) {
-        // A operand i: T[16 mt + lc][16 ks + 4 lg + i], B operand i: R[16 ks + 4 lg + i][lc]
-#pragma unroll
-        for (int mt = 0; mt < NT; ++mt) {
-          uacc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int ks = 0; ks <= mt; ++ks) {
-            const f32x4 tv = *reinterpret_cast<const f32x4 *>(tb + ((mt * (mt + 1)) / 2 + ks) * (16 * kBP) + lc * kBP + 4 * lg);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) uacc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(tv[i], rreg[ks][i], uacc[mt], 0, 0, 0);
-          }
-        }
-      } else if constexpr (DELTA) {
-        s16x4 rhi[NT], rlo[NT];
-#pragma unroll
-        for (int mt = 0; mt < NT; ++mt) split4(rreg[mt], rhi[mt], rlo[mt]);
-#pragma unroll
-        for (int mt = 0; mt < NT; ++mt) {
-          uacc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int ks = 0; ks <= mt; ++ks) {
-            const f32x4 tv = *reinterpret_cast<const f32x4 *>(tb + ((mt * (mt + 1)) / 2 + ks) * (16 * kBP) + lc * kBP + 4 * lg);
-            s16x4 th, tlo;
-            split4(tv, th, tlo);
-            uacc[mt] = mfma16_split(th, tlo, rhi[ks], rlo[ks], uacc[mt]);
-          }
-        }
-      } else {
-#pragma unroll
-        for (int mt = 0; mt < NT; ++mt) uacc[mt] = rreg[mt];
-      }
       s16x4 uhi[NT], ulo[NT];
-      if constexpr (!F32) {
+      auto blockrow = [&](const float *m, int mt, int ks) {  // this lane's four A elements of block (mt, ks)
+        return *reinterpret_cast<const f32x4 *>(m + ((mt * (mt + 1)) / 2 + ks) * (16 * kBP) + lc * kBP + 4 * lg);
+      };
 #pragma unroll
-        for (int mt = 0; mt < NT; ++mt) split4(uacc[mt], uhi[mt], ulo[mt]);
+      for (int mt = 0; mt < NT; ++mt) {
+        uacc[mt] = rreg[mt];
+        if constexpr (DELTA && F32) {
+          // A operand i: column 16 ks + 4 lg + i of row 16 mt + lc, B operand i: U[16 ks + 4 lg + i][lc]
+#pragma unroll
+          for (int ks = 0; ks < mt; ++ks) {
+            const f32x4 lv = blockrow(tb, mt, ks);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) uacc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(lv[i], uacc[ks][i], uacc[mt], 0, 0, 0);
+          }
+          const f32x4 nv = blockrow(tb, mt, mt), x = uacc[mt];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) uacc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(nv[i], x[i], uacc[mt], 0, 0, 0);
+        } else if constexpr (DELTA) {
+          s16x4 ah, al2, xh, xl2;
+#pragma unroll
+          for (int ks = 0; ks < mt; ++ks) {
+            split4(blockrow(tb, mt, ks), ah, al2);
+            uacc[mt] = mfma16_split(ah, al2, uhi[ks], ulo[ks], uacc[mt]);
+          }
+          split4(uacc[mt], xh, xl2);
+          split4(blockrow(tb, mt, mt), ah, al2);
+          uacc[mt] = mfma16_split(ah, al2, xh, xl2, uacc[mt]);
+        }
+        if constexpr (!F32) split4(uacc[mt], uhi[mt], ulo[mt]);
       }
       // outputs and corrected values of node j at ((b n + j) H + h) dv + col;
       // rows past the last node fall outside the descriptors (the whole offset
@@ -995,7 +972,7 @@ void verify_tile_kernel(VerifyArgs a) {
         f32x4 oacc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks <= mt; ++ks) {
-          const f32x4 av = *reinterpret_cast<const f32x4 *>(ab + ((mt * (mt + 1)) / 2 + ks) * (16 * kBP) + lc * kBP + 4 * lg);
+          const f32x4 av = blockrow(ab, mt, ks);
           if constexpr (F32) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) oacc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], uacc[ks][i], oacc, 0, 0, 0);
@@ -1044,7 +1021,7 @@ int device_cus() {
 constexpr int kLateRounds = 4;
 
 template <int DK, int NP, int CW, int TPW, int KIND, bool F32>
-hipError_t launch_np_fam(const VerifyArgs &a, hipStream_t s) {
+hipError_t launch_np(const VerifyArgs &a, hipStream_t s) {
   using L = Layout<DK, NP, CW, TPW, KIND, F32>;
   const size_t lds = L::kBytes;
   if (lds > kMaxLds) return hipErrorInvalidConfiguration;
@@ -1076,13 +1053,7 @@ hipError_t launch_np_fam(const VerifyArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int DK, int NP, int CW, int TPW, bool F32>
-hipError_t launch_np(const VerifyArgs &a, hipStream_t s) {
-  if (a.family == SLA_FAMILY_GLA) return launch_np_fam<DK, NP, CW, TPW, kKindGates, F32>(a, s);
-  return launch_np_fam<DK, NP, CW, TPW, kKindDelta, F32>(a, s);
-}
-
-template <int DK, bool F32>
+template <int DK, int KIND, bool F32>
 hipError_t launch_dk(const VerifyArgs &a, hipStream_t s) {
   // small trees: two V-tiles of a unit per workgroup once single tiles would
   // fill every CU's four workgroup slots twice over.  The launch is then one
@@ -1092,46 +1063,28 @@ hipError_t launch_dk(const VerifyArgs &a, hipStream_t s) {
   if constexpr (DK <= 128) {
     const int ntiles = (a.dv + kWaveCols * 4 - 1) / (kWaveCols * 4);
     if (a.n <= 32 && ntiles % 2 == 0 && (size_t)a.B * a.H * ntiles >= (size_t)8 * device_cus())
-      return a.n <= 16 ? launch_np<DK, 16, 4, 2, F32>(a, s) : launch_np<DK, 32, 4, 2, F32>(a, s);
+      return a.n <= 16 ? launch_np<DK, 16, 4, 2, KIND, F32>(a, s) : launch_np<DK, 32, 4, 2, KIND, F32>(a, s);
   }
-  if (a.n <= 16) return launch_np<DK, 16, 4, 1, F32>(a, s);
-  if (a.n <= 32) return launch_np<DK, 32, 4, 1, F32>(a, s);
+  if (a.n <= 16) return launch_np<DK, 16, 4, 1, KIND, F32>(a, s);
+  if (a.n <= 32) return launch_np<DK, 32, 4, 1, KIND, F32>(a, s);
   // large trees: two V-tiles per workgroup -- topology, Grams and T serve
   // both, and the second tile's state loads overlap the first tile's U, O
   // and stores; with d_v a multiple of 256, tiles of 128 columns (eight
   // column waves), so that one workgroup covers 256 columns
   if constexpr (DK <= 128) {
-    if (a.dv % 256 == 0) return launch_np<DK, 64, 8, 2, F32>(a, s);
-    if (((a.dv + kWaveCols * 4 - 1) / (kWaveCols * 4)) % 2 == 0) return launch_np<DK, 64, 4, 2, F32>(a, s);
+    if (a.dv % 256 == 0) return launch_np<DK, 64, 8, 2, KIND, F32>(a, s);
+    if (((a.dv + kWaveCols * 4 - 1) / (kWaveCols * 4)) % 2 == 0) return launch_np<DK, 64, 4, 2, KIND, F32>(a, s);
   }
-  return launch_np<DK, 64, 4, 1, F32>(a, s);
+  return launch_np<DK, 64, 4, 1, KIND, F32>(a, s);
 }
 
 }  // namespace
 
-bool parallel_supported(int dk, int dv, int n, int dtype) {
-  // bf16 activations: bf16 matrix cores (q and k exact in bf16, the fp32
-  // operands split hi + lo); fp32 activations: fp32 matrix cores.  A draft
-  // whose stage exceeds the LDS is refused at launch
-  // (hipErrorInvalidConfiguration).
-  return (dtype == SLA_DTYPE_BF16 || dtype == SLA_DTYPE_F32) && (dk == 64 || dk == 128 || dk == 256) &&
-         dv % 16 == 0 && n >= 1 && n <= SLA_MAX_NODES;
-}
-
-template <bool F32>
-hipError_t launch_dtype(const VerifyArgs &a, hipStream_t s) {
-  switch (a.dk) {
-    case 64: return launch_dk<64, F32>(a, s);
-    case 128: return launch_dk<128, F32>(a, s);
-    case 256: return launch_dk<256, F32>(a, s);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-hipError_t launch_verify_parallel(const VerifyArgs &a, int dtype, hipStream_t s) {
-  if (dtype == SLA_DTYPE_BF16) return launch_dtype<false>(a, s);
-  if (dtype == SLA_DTYPE_F32) return launch_dtype<true>(a, s);
-  return hipErrorInvalidConfiguration;
+// One translation unit per (d_k, form of the step, activation type): the
+// build compiles this file once for each, so that they compile in parallel.
+template <>
+hipError_t launch_tile<SLA_TILE_DK, SLA_TILE_GATES != 0, SLA_TILE_F32 != 0>(const VerifyArgs &a, hipStream_t s) {
+  return launch_dk<SLA_TILE_DK, SLA_TILE_GATES ? kKindGates : kKindDelta, SLA_TILE_F32 != 0>(a, s);
 }
 
 }  // namespace sla
