@@ -23,8 +23,6 @@ struct VerifyArgs {
   int32_t family;   // SLA_FAMILY_*: which of alpha, beta the step reads, and the gate layout
   bool chain;
   bool has_pending;
-  bool late_state;  // parallel route: issue the state reads after the first barrier
-  bool stagger;     // parallel route: hold the state reads back briefly (a full round of workgroups)
   bool write_through;  // 1-node kernel: committed rows written through at device scope
   bool xcd_group;      // 1-node kernel: a unit's slabs numbered back to back on one XCD
   float *state;

@@ -66,6 +66,7 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int kWaveCols = 16;                    // state columns per column wave
 constexpr int kPMax = 8;                          // pending steps staged in LDS
@@ -84,6 +85,24 @@ constexpr int kBP = 20;                           // fp32 row pitch of a 16x16 b
 //               O = Q~ H0 + Attn V with Q~_j = Gamma_j * q_j (fp32, split
 //               into bf16 hi + lo).
 constexpr int kKindDelta = 0, kKindGates = 1;
+
+// Launches by their rounds of workgroups (resident workgroups per CU from the
+// occupancy of the kernel instantiation):
+//   kModePart   less than one round, or rows that are not whole 128-byte
+//               lines: the state reads go out before the first barrier, so
+//               that they overlap the setup wave's dependent reads, and
+//               committed rows are written back;
+//   kModeRound  one to kLateRounds rounds: committed rows are written through
+//               (64 16-node trees, 16 heads, over 24 rotating layers: 36.7 us,
+//               38.7 us written back; with d_v 144, whose rows split lines,
+//               writing back is better: 23 nodes, 12 heads, batch 40, per-key
+//               gates 37.7 us, 39.7 us through);
+//   kModeLate   kLateRounds rounds or more: the state reads go out after the
+//               first barrier (64-node trees at batch 256, eight rounds: 419 us,
+//               432 us with the reads first).
+// Template parameters: a run-time choice of the store policy or of the place
+// of the state reads costs most of what it gains.
+constexpr int kModePart = 0, kModeRound = 1, kModeLate = 2;
 
 // F32: fp32 activations.  q, k, v and the pending keys are staged and read
 // as fp32, and every contraction runs on v_mfma_f32_16x16x4_f32 with exact
@@ -131,12 +150,12 @@ __device__ __forceinline__ int xchunk(int row, int c) {
 constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 
 // element (row j, column a), a <= j, of a lower-triangular 16x16-blocked matrix
-__device__ __forceinline__ int blk(int j, int a) {
+[[maybe_unused]] __device__ __forceinline__ int blk(int j, int a) {
   const int bj = j >> 4;
   return ((bj * (bj + 1)) / 2 + (a >> 4)) * (16 * kBP) + (j & 15) * kBP + (a & 15);
 }
 
-__device__ __forceinline__ void split8(const float (&x)[8], bf16x8 &hi, bf16x8 &lo) {
+[[maybe_unused]] __device__ __forceinline__ void split8(const float (&x)[8], bf16x8 &hi, bf16x8 &lo) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const __bf16 h = static_cast<__bf16>(x[e]);
@@ -145,7 +164,7 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8 &hi, bf16x8 &
   }
 }
 
-__device__ __forceinline__ void split4(f32x4 x, s16x4 &hi, s16x4 &lo) {
+[[maybe_unused]] __device__ __forceinline__ void split4(f32x4 x, s16x4 &hi, s16x4 &lo) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const __bf16 h = static_cast<__bf16>(x[e]);
@@ -154,13 +173,13 @@ __device__ __forceinline__ void split4(f32x4 x, s16x4 &hi, s16x4 &lo) {
   }
 }
 
-__device__ __forceinline__ f32x4 mfma16(s16x4 a, s16x4 b, f32x4 c) {
+[[maybe_unused]] __device__ __forceinline__ f32x4 mfma16(s16x4 a, s16x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
 
 // acc += A B with A and B fp32 given as hi + lo (the lo * lo term is below
 // fp32 resolution and dropped).
-__device__ __forceinline__ f32x4 mfma16_split(s16x4 ah, s16x4 al, s16x4 bh, s16x4 bl, f32x4 acc) {
+[[maybe_unused]] __device__ __forceinline__ f32x4 mfma16_split(s16x4 ah, s16x4 al, s16x4 bh, s16x4 bl, f32x4 acc) {
   acc = mfma16(ah, bh, acc);
   acc = mfma16(ah, bl, acc);
   return mfma16(al, bh, acc);
@@ -174,8 +193,7 @@ template <int DK, int NP, int CW, bool F32>
 constexpr int kMinWaves = F32 ? 1 : ((DK <= 128 && NP <= 16) ? 6 : (CW == 8 ? 4 : 1));
 
 // KIND: the family's form (see Layout).  Without the delta rule Lk = 0, so
-// T = I and U = R = V: no P_k, no Lk, no T.  WT: committed rows written
-// through at device scope (launches of one full round of workgroups).
+// T = I and U = R = V: no P_k, no Lk, no T.
 // eight column waves: column wave 0 also does the setup work, so that the
 // workgroup is eight waves and two fit a CU at 124 VGPRs (a ninth wave keeps
 // it to one: measured on 64-node trees at batch 64, d_v 256, 459 -> 448 us per
@@ -183,16 +201,20 @@ constexpr int kMinWaves = F32 ? 1 : ((DK <= 128 && NP <= 16) ? 6 : (CW == 8 ? 4 
 template <int CW>
 constexpr int kWaves = CW == 8 ? CW : CW + 1;
 
-template <int DK, int NP, int CW, int TPW, int KIND, bool F32, bool WT>
+// MODE: how a launch's rounds of workgroups order the state reads (kMode*).
+template <int DK, int NP, int CW, int TPW, int KIND, bool F32, int MODE>
 __global__ __launch_bounds__(kWaves<CW> * kWave) __attribute__((amdgpu_waves_per_eu(kMinWaves<DK, NP, CW, F32>)))
 void verify_tile_kernel(VerifyArgs a) {
   using L = Layout<DK, NP, CW, TPW, KIND, F32>;
   using AT = std::conditional_t<F32, float, bf16>;  // activation element
+  using VT = std::conditional_t<F32, uint32_t, uint16_t>;  // its bit pattern
   constexpr int ES = L::ES;
   constexpr int EC = 16 / ES;  // activations per 16-byte chunk
   constexpr bool DELTA = KIND == kKindDelta;
   constexpr bool GV = KIND == kKindGates;
   const bool nodelta = !DELTA || a.family == SLA_FAMILY_DECAY;  // R = V
+  constexpr bool kLate = MODE == kModeLate;
+  constexpr bool WT = MODE == kModeRound;       // committed rows written through at device scope
   constexpr int kColWaves = CW;                 // waves 0 .. CW-1 own state columns
   constexpr int kSetup = kWaves<CW> == CW ? 0 : CW;  // the setup wave
   constexpr int kTileCols = L::kTileCols;       // state columns per workgroup
@@ -241,9 +263,13 @@ void verify_tile_kernel(VerifyArgs a) {
                               ((uint32_t)(n - 1) * nstride + dv) * ES);
   // wave-uniform: this wave owns columns of tile t
   auto live = [&](int t) { return w < kColWaves && t * kTileCols + w * kWaveCols < dv; };
+  // a wave past the last column reads outside the descriptors (zeros, no
+  // traffic) instead of branching round its reads: the compiler then counts
+  // the reads in flight exactly
+  auto outside = [&](int t) { return live(t) ? 0u : 0x80000000u; };
   // state rows 8 lg + e + 32 ks of column t * kTileCols + ucol, in B-fragment order
   auto load_state = [&](int t, float (&hf)[KS][8], int ks0 = 0) {
-    const uint32_t sv = (uint32_t)(8 * lg * dv + t * kTileCols + ucol) * 4;
+    const uint32_t sv = (uint32_t)(8 * lg * dv + t * kTileCols + ucol) * 4 | outside(t);
 #pragma unroll
     for (int ks = ks0; ks < KS; ++ks)
 #pragma unroll
@@ -251,13 +277,14 @@ void verify_tile_kernel(VerifyArgs a) {
   };
   // values of node j = 16 mt + 4 lg + q; rows past the last node fall
   // outside the descriptor and read zero
-  auto load_values = [&](int t, uint32_t (&vraw)[NT][4]) {
+  auto load_values = [&](int t, VT (&vraw)[NT][4]) {
     const uint32_t vv = (4 * lg * nstride + t * kTileCols + ucol) * ES;
+    const uint32_t ov = outside(t);
 #pragma unroll
     for (int mt = 0; mt < NT; ++mt)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const uint32_t o = vv + (uint32_t)(mt * 16 + q) * nstride * ES;
+        const uint32_t o = (vv + (uint32_t)(mt * 16 + q) * nstride * ES) | ov;
         if constexpr (F32)
           vraw[mt][q] = __builtin_amdgcn_raw_buffer_load_b32(vr, o, 0, kPolicyDefault);
         else
@@ -275,116 +302,238 @@ void verify_tile_kernel(VerifyArgs a) {
     x[0] = u0.x, x[1] = u0.y, x[2] = u0.z, x[3] = u0.w, x[4] = u1.x, x[5] = u1.y, x[6] = u1.z, x[7] = u1.w;
   };
 
-  // ---- column waves: the first tile's state and values, issued first
-  float hfa[KS][8], hfb[KS][8];  // hfb: the next tile's state (prefetching form only)
-  uint32_t vraw[NT][4];  // activation bit patterns, widened where they are used
-  if (live(t0)) {
-    // a full round of workgroups: hold the state reads back about two
-    // microseconds (80 x 64 cycles), so that every workgroup's setup reads
-    // and [Q; K] enter the memory queue ahead of the state (measured per
-    // launch against no delay: 20 -> +1.6%, 40 -> -1.0%, 64 -> -1.7%,
-    // 80 -> -2.1%, 100 -> -1.7%)
-    if (a.stagger && w != kSetup) __builtin_amdgcn_s_sleep(80);
-    if (!a.late_state) load_state(t0, hfa);
-    load_values(t0, vraw);
-  }
-
-  // ---- setup wave: everything that depends on another read
-  int p = -1;      // setup wave, lane j: parent of node j
-  float al = 1.f;  // setup wave, lane j: alpha_j
-  int nodec = 0;   // setup wave, lane t: node of pending step t (clamped into the store)
-  int maxd = 0;    // setup wave: the deepest root path (wave-uniform)
+  // ---- setup wave: the small reads, ahead of everything else: parent row,
+  //      gates, and the pending accepted path with the previous round's parent
+  //      row and gates read whole, so that validating the path waits on no
+  //      further read
+  int p = -1;       // lane j: parent of node j
+  float al = 1.f;   // lane j: alpha_j
+  float be = 0.f;   // lane j: beta_j
+  int plen = 0;     // accepted length
+  int nodec = -1;   // lane t: node of pending step t (later clamped into the store)
+  int prow_parent = -2;
+  float pal = 0.f;  // lane t: gate of pending record t (later of step t's record)
+  const int pn = a.has_pending ? a.pend.n : 1;
+  const size_t prow = (size_t)b * pn;
+  const int ln = l < n ? l : n - 1, lp = l < pn ? l : pn - 1;  // lanes past the last node re-read it
   if (w == kSetup) {
-    for (int c = l; c < (L::kT + L::kAt) / 16; c += kWave) reinterpret_cast<uint4 *>(tb)[c] = make_uint4(0, 0, 0, 0);
-    const AT *qg = static_cast<const AT *>(a.q);
-    const AT *kg = static_cast<const AT *>(a.k);
-    const bool live = l < n;
-    const size_t s = (nbase + (live ? l : 0)) * H + h;
-    p = live ? a.parent[nbase + l] : -1;
+    p = a.parent[nbase + ln];
     // DeltaNet: no decay; GLA: the per-key gates enter through Q~ and Attn
-    al = (!GV && live && a.family != SLA_FAMILY_DELTANET) ? a.alpha[s] : 1.f;
-    const float be = (DELTA && live && a.family != SLA_FAMILY_DECAY) ? a.beta[s] : 0.f;
-    // pending accepted path, with the previous round's parent row and gates
-    // read whole, so that validating the path waits on no further read
-    int plen = 0, node = -1, prow_parent = -2;
-    float prow_alpha = 0.f;
-    const int pn = a.has_pending ? a.pend.n : 1;
-    const size_t prow = (size_t)b * pn;
+    if (!GV && a.family != SLA_FAMILY_DELTANET) al = a.alpha[(nbase + ln) * H + h];
+    if (DELTA && a.family != SLA_FAMILY_DECAY) be = a.beta[(nbase + ln) * H + h];
     if (a.has_pending) {
       plen = a.pend.len[b];
-      node = l < pn ? a.pend.path[prow + l] : -1;
-      prow_parent = l < pn ? a.pend.parent[prow + l] : -2;
-      prow_alpha = (!GV && l < pn) ? a.pend.alpha[(prow + l) * H + h] : 0.f;
+      nodec = a.pend.path[prow + lp];
+      prow_parent = a.pend.parent[prow + lp];
+      if (!GV) pal = a.pend.alpha[(prow + lp) * H + h];
     }
-    // [Q; K] straight into LDS (rows 0..NP-1: q_j, NP..2NP-1: k_j; padding
-    // rows repeat node 0 and are never used)
-#pragma unroll 1
-    for (int i = 0; i < 2 * NP * CH / kWave; ++i) {
-      const int P = i * kWave + l;
+  }
+
+  // ---- column waves: [Q; K] (and GLA's gates) on their way to LDS through
+  //      registers, a share per wave (rows 0..NP-1: q_j, NP..2NP-1: k_j; rows
+  //      past the last node fall outside the descriptors and read zero), then
+  //      the first tile's state and values.  The stores to LDS wait for their
+  //      own reads only, not for the state behind them.  (The setup wave used
+  //      to bring [Q; K] by itself, straight into LDS, and every LDS operation
+  //      behind it waited.)
+  constexpr int kLanes = kColWaves * kWave;
+  constexpr int NQ = 2 * NP * CH / kLanes;           // 16-byte chunks per lane
+  constexpr int GC = DK / 4;                         // 16-byte chunks per gate row
+  constexpr int NG = GV ? NP * GC / kLanes : 0;
+  float hfa[KS][8], hfb[KS][8];  // hfb: the next tile's state (prefetching form only)
+  VT vraw[NT][4];  // activation bit patterns, widened where they are used
+  auto column_reads = [&]() {
+    const uint32_t rowb = (uint32_t)H * DK;  // elements between consecutive nodes of a unit
+    const uint32_t qkb = ((uint32_t)(n - 1) * rowb + DK) * ES;
+    const rsrc_t qr = make_rsrc(static_cast<const AT *>(a.q) + (nbase * H + h) * DK, qkb);
+    const rsrc_t kr = make_rsrc(static_cast<const AT *>(a.k) + (nbase * H + h) * DK, qkb);
+    u32x4 qk[NQ], gq[NG > 0 ? NG : 1];
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const int P = i * kLanes + w * kWave + l;
       const int row = P / CH, c = (P % CH) ^ (row & 7);
-      const int j = row % NP;
-      load_lds16((row < NP ? qg : kg) + ((nbase + (j < n ? j : 0)) * H + h) * DK + c * EC, xs + i * kWave);
+      const bool isq = i * kLanes + w * kWave < NP * CH;  // wave-uniform: a wave's rows lie in one half
+      qk[i] = __builtin_amdgcn_raw_buffer_load_b128(isq ? qr : kr, ((uint32_t)(row % NP) * rowb + c * EC) * ES, 0,
+                                                    kPolicyDefault);
     }
-    if constexpr (GV) {  // the draft's per-key gates, rows 0..NP-1 (padding rows repeat node 0)
-      constexpr int GC = DK / 4;  // 16-byte chunks per gate row
-#pragma unroll 1
-      for (int i = 0; i < NP * GC / kWave; ++i) {
-        const int P = i * kWave + l;
-        const int j = P / GC;
-        load_lds16(a.alpha + ((nbase + (j < n ? j : 0)) * H + h) * DK + (P % GC) * 4, s_g + i * kWave * 4);
+    if constexpr (GV) {
+      const rsrc_t gr = make_rsrc(a.alpha + (nbase * H + h) * DK, ((uint32_t)(n - 1) * rowb + DK) * 4);
+#pragma unroll
+      for (int i = 0; i < NG; ++i) {
+        const int P = i * kLanes + w * kWave + l;
+        gq[i] = __builtin_amdgcn_raw_buffer_load_b128(gr, ((uint32_t)(P / GC) * rowb + (P % GC) * 4) * 4, 0, kPolicyDefault);
       }
     }
+    __builtin_amdgcn_sched_barrier(0);  // none of these moves behind the state reads
+    // hold the state reads back about 0.8 us (30 x 64 cycles), so that the
+    // setup reads and [Q; K] enter the memory queue ahead of the state
+    // (measured per launch with no hold and with 20, 30, 45: batch 1, 8 nodes
+    // 7.19, 7.28, 6.90, 7.04 us; batch 16, 16 nodes 12.05, 11.42, 11.58,
+    // 11.22 us); a full round of workgroups a little longer (64 16-node trees
+    // over 24 rotating layers with 30, 50, 80, 127: 36.9, 36.7, 36.9, 38.0 us)
+    if (!kLate && w != kSetup) __builtin_amdgcn_s_sleep(MODE == kModeRound ? 50 : 30);
+    if constexpr (!kLate && kSetup != 0) load_state(t0, hfa);
+    load_values(t0, vraw);
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) reinterpret_cast<u32x4 *>(xs)[i * kLanes + w * kWave + l] = qk[i];
+    if constexpr (GV) {
+#pragma unroll
+      for (int i = 0; i < NG; ++i) reinterpret_cast<u32x4 *>(s_g)[i * kLanes + w * kWave + l] = gq[i];
+    }
+  };
 
-    // topology, decays and compact-list offsets; lane j owns node j
+  // ---- setup wave: the records of kPMax steps of the accepted path, from
+  //      step c0 on, for the columns of TPW tiles or of one: read into
+  //      registers (node indices are clamped into the store), then put into
+  //      the LDS stage
+  constexpr int KI = kPMax * CH / kWave;            // 16-byte key chunks per lane
+  constexpr int GI = GV ? kPMax * GC / kWave : 0;   // 16-byte gate chunks per lane
+  constexpr int UC = kTileCols / kWave;             // corrected values per lane, step and tile
+  struct Records {
+    u32x4 k[KI];
+    float u[TPW][kPMax * UC];
+  };
+  // (32-bit offsets from the unit's first record: one sequence's rows of one
+  // tensor stay below 2^31 bytes)
+  const AT *const pk0 = static_cast<const AT *>(a.pend.k) + (prow * H + h) * DK;
+  const float *const pg0 = a.pend.alpha + (prow * H + h) * DK;
+  const float *const pu0 = a.pend.u + (prow * H + h) * dv;
+  const uint32_t krow = (uint32_t)H * DK;
+  auto key_at = [&](int c0, int i) {  // this lane's i-th 16-byte key chunk of the stage
+    return __umul24(__shfl(nodec, c0 + (i * kWave + l) / CH), krow) + ((i * kWave + l) % CH) * EC;
+  };
+  auto gate_at = [&](int c0, int i) {
+    return __umul24(__shfl(nodec, c0 + (i * kWave + l) / GC), krow) + ((i * kWave + l) % GC) * 4;
+  };
+  auto u_row = [&](int c0, int st) { return (uint32_t)__builtin_amdgcn_readlane(nodec, c0 + st) * nstride; };
+  auto u_col = [&](int i, int u) {  // tile t0 + i, column block u; columns past d_v re-read the last
+    const int cg = (t0 + i) * kTileCols + u * kWave + l;
+    return (uint32_t)(cg < dv ? cg : dv - 1);
+  };
+  auto gather_gates = [&](int c0) {
+    uint32_t gp[GI > 0 ? GI : 1];
+#pragma unroll
+    for (int x = 0; x < GI; ++x) gp[x] = gate_at(c0, x);
+    __builtin_amdgcn_sched_barrier(0);  // an LDS operation after a direct load waits for it
+#pragma unroll
+    for (int x = 0; x < GI; ++x) load_lds16(pg0 + gp[x], s_pg + x * kWave * 4);
+  };
+  // the first steps' records, every tile's values: through registers (GLA's
+  // gate rows straight into LDS)
+  auto read_records = [&](Records &r) {
+    const rsrc_t kr = make_rsrc(pk0, ((uint32_t)(pn - 1) * krow + DK) * ES);
+    const rsrc_t ur = make_rsrc(pu0, ((uint32_t)(pn - 1) * nstride + dv) * 4);
+#pragma unroll
+    for (int i = 0; i < KI; ++i) r.k[i] = __builtin_amdgcn_raw_buffer_load_b128(kr, key_at(0, i) * ES, 0, kPolicyDefault);
+#pragma unroll
+    for (int i = 0; i < TPW; ++i)
+#pragma unroll
+      for (int st = 0; st < kPMax; ++st)
+#pragma unroll
+        for (int u = 0; u < UC; ++u) r.u[i][st * UC + u] = buf_load_f32<kPolicyDefault>(ur, u_col(i, u) * 4, u_row(0, st) * 4);
+  };
+  auto stage_records = [&](const Records &r) {
+#pragma unroll
+    for (int i = 0; i < KI; ++i) reinterpret_cast<u32x4 *>(s_pk)[i * kWave + l] = r.k[i];
+    if (l < kPMax) s_palpha[l] = pal;
+#pragma unroll
+    for (int i = 0; i < TPW; ++i)
+#pragma unroll
+      for (int st = 0; st < kPMax; ++st)
+#pragma unroll
+        for (int u = 0; u < UC; ++u) s_pu[(i * kPMax + st) * kTileCols + u * kWave + l] = r.u[i][st * UC + u];
+    gather_gates(0);
+  };
+  // the records of steps c0 .. c0 + kPMax - 1 for tile t0 + i, straight into
+  // LDS (no registers: the column waves' state is in theirs)
+  auto restage_records = [&](int c0, int i) {
+    if (l >= c0 && l < c0 + kPMax) s_palpha[l - c0] = pal;
+    uint32_t kp[KI];
+#pragma unroll
+    for (int x = 0; x < KI; ++x) kp[x] = key_at(c0, x);
+    __builtin_amdgcn_sched_barrier(0);  // an LDS operation after a direct load waits for it
+#pragma unroll
+    for (int x = 0; x < KI; ++x) load_lds16(pk0 + kp[x], s_pk + x * kWave * EC);
+#pragma unroll
+    for (int st = 0; st < kPMax; ++st)
+#pragma unroll
+      for (int u = 0; u < UC; ++u) load_lds4(pu0 + u_row(c0, st) + u_col(i, u), s_pu + (i * kPMax + st) * kTileCols + u * kWave);
+    gather_gates(c0);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  };
+
+  // ---- setup wave: path check, topology
+  int maxd = 0;    // the deepest root path (wave-uniform)
+  auto setup = [&](Records &rec) {
+    const bool live = l < n;
+    if (!live) p = -1;
+    auto up = [](int x, int v) { return __shfl(v, x >= 0 ? x : 0); };
+    auto upf = [](int x, float v) { return __shfl(v, x >= 0 ? x : 0); };
+    // The path: step t is node path[t], whose parent must be path[t - 1] (-1
+    // for t = 0).  Root paths: p_s is a node's s-th ancestor (-1 past the
+    // root) and g_s the product of the gates of its first s path nodes, itself
+    // included: D_jx = g_s for the ancestor x = p_s.  (An LDS round trip per
+    // line of lane reads: independent ones share a line.)
+    const int node = a.has_pending && l < pn ? nodec : -1;
+    const bool inrange = node >= 0 && node < pn;
+    nodec = inrange ? node : 0;
+    const int prev = __builtin_amdgcn_update_dpp(-1, node, 0x138, 0xf, 0xf, false);  // wave_shr:1, -1 into lane 0
+    int xw[4];
+    float gw[4];
+    const int ppar = __shfl(prow_parent, nodec), pa = up(p, p);
+    const float pgate = __shfl(pal, nodec), ga = upf(p, al);
+    pal = pgate;
+    const bool pbad = a.has_pending && wave_any((plen < 0 || plen > pn) || (l < plen && (!inrange || ppar != prev)));
+    if (a.has_pending) read_records(rec);  // at once, ahead of the topology
+    xw[0] = p;
+    gw[0] = al;
+    xw[1] = p >= 0 ? pa : -1;
+    gw[1] = p >= 0 ? al * ga : al;
+    const int pb = up(xw[1], p), pc = up(xw[1], xw[1]);
+    const float gb = upf(xw[1], al), gc = upf(xw[1], gw[1]);
+    for (int c = l; c < (L::kT + L::kAt) / 16; c += kWave) reinterpret_cast<uint4 *>(tb)[c] = make_uint4(0, 0, 0, 0);
+    xw[2] = xw[1] >= 0 ? pb : -1;
+    gw[2] = xw[1] >= 0 ? gw[1] * gb : gw[1];
+    xw[3] = xw[1] >= 0 ? pc : -1;
+    gw[3] = xw[1] >= 0 ? gw[1] * gc : gw[1];
+    const int p4 = xw[3];
+    const float g4 = gw[3];
+
+    // topology and decays; lane j owns node j
     bool bad = live && (p < -1 || p >= l);
     if (a.chain) bad = bad || (live && p != l - 1);
     int err = wave_any(bad) ? SLA_ERR_TOPOLOGY : SLA_OK;
     if (err == SLA_OK) {
-      // Root paths.  p_s is a node's s-th ancestor (-1 past the root) and g_s
-      // the product of the gates of its first s path nodes, itself included:
-      // D_jx = g_s for the ancestor x = p_s.  Four walkers per lane start at
-      // ancestors 1 to 4 and hop four at a time (their lane reads are
-      // independent, so a round costs about one of them); the scalar families
-      // park each D_jx at (j, x) of the Attn and the Lk blocks for the Grams.
-      // Products of gates only: they may underflow, never overflow (no
-      // reciprocal of a decay product anywhere).  One hop per ancestor took
-      // 10 us of a 48-node chain's launch.
+      // Four walkers per lane start at ancestors 1 to 4 and hop four at a time;
+      // the scalar families park each D_jx at (j, x) of the Attn and the Lk
+      // blocks for the Grams.  Products of gates only: they may underflow,
+      // never overflow (no reciprocal of a decay product anywhere).  One hop
+      // per ancestor took 10 us of a 48-node chain's launch.
       uint64_t m = live ? (1ull << l) : 0ull;
-      auto up = [](int x, int v) { return __shfl(v, x >= 0 ? x : 0); };
-      auto upf = [](int x, float v) { return __shfl(v, x >= 0 ? x : 0); };
-      int xw[4];
-      float gw[4];
-      xw[0] = p;
-      gw[0] = al;
-      {
-        const int pa = up(p, p);
-        const float ga = upf(p, al);
-        xw[1] = p >= 0 ? pa : -1;
-        gw[1] = p >= 0 ? al * ga : al;
-        const int pb = up(xw[1], p), pc = up(xw[1], xw[1]);
-        const float gb = upf(xw[1], al), gc = upf(xw[1], gw[1]);
-        xw[2] = xw[1] >= 0 ? pb : -1;
-        gw[2] = xw[1] >= 0 ? gw[1] * gb : gw[1];
-        xw[3] = xw[1] >= 0 ? pc : -1;
-        gw[3] = xw[1] >= 0 ? gw[1] * gc : gw[1];
-      }
-      const int p4 = xw[3];
-      const float g4 = gw[3];
-      if (DELTA && live) ab[blk(l, l)] = 1.f;
+      // block entry (l, x) is at row0 + x + 304 (x / 16) floats
+      const int row0 = ((l >> 4) * ((l >> 4) + 1) / 2) * (16 * kBP) + (l & 15) * kBP;
+      static_assert(16 * kBP - 16 == 304, "block pitch");
+      if (DELTA && live) ab[row0 + (l >> 4) * 304 + l] = 1.f;
       while (wave_any(xw[0] >= 0)) {
+        int px[4];
+        float gx[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          px[r] = up(xw[r], p4);
+          gx[r] = upf(xw[r], g4);
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int x = xw[r];
-          const int px = up(x, p4);
-          const float gx = upf(x, g4);
           if (x >= 0) {
             if constexpr (DELTA) {
-              ab[blk(l, x)] = gw[r];
-              tb[blk(l, x)] = gw[r];
+              const int at = row0 + (x >> 4) * 304 + x;
+              ab[at] = gw[r];
+              tb[at] = gw[r];
             }
             m |= 1ull << x;
-            gw[r] *= gx;  // walker 0, once past the root: the gates of the whole path
-            xw[r] = px;
+            gw[r] *= gx[r];  // walker 0, once past the root: the gates of the whole path
+            xw[r] = px[r];
           }
         }
       }
@@ -400,82 +549,21 @@ void verify_tile_kernel(VerifyArgs a) {
         s_be[l] = be;
       }
     }
-    // the path: step t is node path[t], whose parent must be path[t - 1]
-    // (-1 for t = 0)
-    const bool inrange = node >= 0 && node < pn;
-    nodec = inrange ? node : 0;
-    if (err == SLA_OK && a.has_pending) {
-      int prev = __shfl_up(node, 1);
-      if (l == 0) prev = -1;
-      const int ppar = __shfl(prow_parent, nodec);
-      const float pal = __shfl(prow_alpha, nodec);
-      const bool step = l < plen;
-      const bool pbad = (plen < 0 || plen > pn) || (step && (!inrange || ppar != prev));
-      err = wave_any(pbad) ? SLA_ERR_PATH : SLA_OK;
-      if (l < kPMax) s_palpha[l] = l < plen ? pal : 0.f;
-    }
+    if (err == SLA_OK && pbad) err = SLA_ERR_PATH;
     if (l == 0) {
       s_misc[0] = err;
       s_misc[1] = plen;
       s_misc[2] = maxd;
     }
     if (t0 == 0 && h == 0 && l == 0 && a.status) a.status[b] = err;
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // [Q; K] has landed
-  }
-  __syncthreads();
-  const int err = s_misc[0];
-  if (err != SLA_OK) return;
-  // many rounds of workgroups: the state goes out only now, behind the small
-  // reads the setup wave waits for
-  if (kSetup != 0 && a.late_state && live(t0)) load_state(t0, hfa);
-  const int plen = s_misc[1];
-
-  // ---- setup wave: records of the first kPMax path nodes, gathered straight
-  //      into LDS while the column waves compute; a gather is the wave's
-  //      only LDS write until the next barrier, which waits for it
-  const size_t prow = (size_t)b * (a.has_pending ? a.pend.n : 1);
-  // corrected values of tile t (its columns) into stage buffer `buf`
-  auto gather_u = [&](int t, int buf) {
-#pragma unroll
-    for (int st = 0; st < kPMax; ++st) {
-      const int ntt = __builtin_amdgcn_readlane(nodec, st);
-#pragma unroll
-      for (int c0 = 0; c0 < kTileCols; c0 += kWave) {
-        const int cg = t * kTileCols + c0 + l;
-        load_lds4(a.pend.u + ((prow + ntt) * H + h) * dv + (cg < dv ? cg : dv - 1),
-                  s_pu + (buf * kPMax + st) * kTileCols + c0);
-      }
-    }
   };
-  if (w == kSetup && a.has_pending) {
-    const AT *pkg = static_cast<const AT *>(a.pend.k);
-    constexpr int KI = kPMax * CH / kWave;
-    constexpr int GC = DK / 4;                             // 16-byte chunks per gate row
-    constexpr int GI = GV ? kPMax * GC / kWave : 0;
-    int nt[KI], ng[GI > 0 ? GI : 1];  // node of the step whose key (gate) chunk this lane gathers
-#pragma unroll
-    for (int i = 0; i < KI; ++i) nt[i] = __shfl(nodec, (i * kWave + l) / CH);
-#pragma unroll
-    for (int i = 0; i < GI; ++i) ng[i] = __shfl(nodec, (i * kWave + l) / GC);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < KI; ++i)
-      load_lds16(pkg + ((prow + nt[i]) * H + h) * DK + ((i * kWave + l) % CH) * EC, s_pk + i * kWave * EC);
-#pragma unroll
-    for (int i = 0; i < GI; ++i)
-      load_lds16(a.pend.alpha + ((prow + ng[i]) * H + h) * DK + ((i * kWave + l) % GC) * 4, s_pg + i * kWave * 4);
-    // every tile's values at once: a later tile's would otherwise be waited
-    // for on the critical path
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) gather_u(t0 + i, i);
-  }
   // ---- setup wave: the second tile's first DK/2 state rows into LDS, queued
-  //      behind the record gathers.  Chunk c holds row r = c / 16, column
+  //      behind the records.  Chunk c holds row r = c / 16, column
   //      chunk (c % 16) ^ 4 ((r / 8) % 4), so that the 16 column-wave lanes of
   //      a row group and the four row groups fall on distinct banks.  Columns
   //      past d_v (a ragged last tile) re-read column 0 and are never used.
-  if constexpr (L::kPrefetch) {
-    if (w == kSetup) {
+  auto stage_second_tile = [&]() {
+    if constexpr (L::kPrefetch) {
       const int cb = (t0 + 1) * kTileCols;
 #pragma unroll
       for (int m = 0; m < L::kPreInstr; ++m) {
@@ -485,7 +573,7 @@ void verify_tile_kernel(VerifyArgs a) {
         load_lds16(a.state + (unit * DK + r) * dv + (col < dv ? col : 0), s_pre + m * kWave * 4);
       }
     }
-  }
+  };
 
   // ---- GLA: the tree-masked scores with per-key decay ratios,
   //          Attn_ja = sum_i q_j[i] D_ja[i] k_a[i],  D_ja = product of the
@@ -497,8 +585,8 @@ void verify_tile_kernel(VerifyArgs a) {
   //      place of q_j) + lo for P_q = Q~ H0.  Gate products only: they may
   //      underflow, never overflow.  The records (the key as given, the
   //      gates) are written from here.
-  if constexpr (GV) {
-    if (w < kColWaves) {
+  auto gate_scores = [&]() {
+    if constexpr (GV) {
       constexpr int E = DK / 16;  // key dimensions per lane
       const int maxd = s_misc[2];
       unsigned char *xb = reinterpret_cast<unsigned char *>(xs);
@@ -621,18 +709,15 @@ void verify_tile_kernel(VerifyArgs a) {
         }
       }
     }
-    __syncthreads();
-  }
-
-  // the folded setup wave's own state reads go out after its record gathers
-  if (kSetup == 0 && a.late_state && live(t0)) load_state(t0, hfa);
+  };
 
   // ---- tree-masked Grams over the column waves (scalar gates; GLA's scores
   //      were formed above): tile (mr, na) of [Q; K] K^T holds rows of node
   //      tile mr % NT against ancestor candidates of node tile na <= mr % NT;
   //      ancestor entries go to Attn blocks and Lk lists
-  if constexpr (!GV) {
-    f32x4 gacc[GT];
+  auto grams = [&]() {
+    if constexpr (!GV) {
+      f32x4 gacc[GT];
     int tc = 0;
 #pragma unroll
     for (int mr = 0; mr < MT; ++mr)
@@ -664,30 +749,72 @@ void verify_tile_kernel(VerifyArgs a) {
         if (tc % kColWaves != w || (mr % NT) * 16 >= n || (!DELTA && mr >= NT)) continue;
         // every LDS read of the tile's metadata is issued before its first
         // write, so they share one round trip
+        const int bj = mr % NT;
         const int an = na * 16 + lc;
-        const int jb = (mr % NT) * 16 + 4 * lg;
+        const int jb = bj * 16 + 4 * lg;
         uint32_t anc[4];  // the half of row j's ancestor mask that holds column an
-        float dj[4], bj[4];  // dj: decay ratio D_{j,an}, parked where the entry goes
-        float *const db = mr < NT ? ab : tb;
+        float dj[4], be4[4];  // dj: decay ratio D_{j,an}, parked where the entry goes
+        float *const db = (mr < NT ? ab : tb) + ((bj * (bj + 1)) / 2 + na) * (16 * kBP) + 4 * lg * kBP + lc;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           anc[q] = reinterpret_cast<const uint32_t *>(s_anc)[2 * (jb + q) + (na >> 1)];
-          dj[q] = db[blk(jb + q, an)];  // an <= 16 (jb / 16) + 15: inside the block row
-          if (mr >= NT) bj[q] = s_be[jb + q];
+          dj[q] = db[q * kBP];
+          be4[q] = mr >= NT ? s_be[jb + q] : 0.f;
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int j = jb + q;
-          // rows past the last node hold stale LDS words: masked by j < n
-          if (j >= n || an > j || (mr >= NT && an == j) || !((anc[q] >> (an & 31)) & 1u)) continue;
+          // every entry is written: zero unless an is an ancestor of j (rows
+          // past the last node hold stale LDS words: masked by j < n; the
+          // diagonal of Lk is not read)
+          const bool on = j < n && an <= j && !(mr >= NT && an == j) && ((anc[q] >> (an & 31)) & 1u);
           const float dg = dj[q] * gacc[tc / kColWaves][q];
-          db[blk(j, an)] = mr < NT ? dg : -(bj[q] * dg);
+          db[q * kBP] = on ? (mr < NT ? dg : -(be4[q] * dg)) : 0.f;
         }
       }
+    }
+  };
+
+  // ---- the two kinds of waves up to the barrier behind which the Grams and
+  //      the records are complete: branches of their own (the wave number is
+  //      scalar), so that neither's registers are live, nor its outstanding
+  //      reads waited for, in the other
+  if constexpr (kSetup == 0) {
+    column_reads();
+    if (w == kSetup) {
+      Records rec;
+      setup(rec);
+      if (a.has_pending) stage_records(rec);
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+      if constexpr (!kLate) load_state(t0, hfa);  // its own state: after its record reads
+    } else if constexpr (!kLate) {
+      load_state(t0, hfa);
+    }
+    __syncthreads();
+    if (s_misc[0] != SLA_OK) return;
+    gate_scores();
+    if constexpr (kLate) load_state(t0, hfa);
+    grams();
+  } else if (w != kSetup) {
+    column_reads();
+    __syncthreads();
+    if (s_misc[0] != SLA_OK) return;
+    // many rounds of workgroups: the state goes out only now, behind the small
+    // reads the setup wave waits for
+    if constexpr (kLate) load_state(t0, hfa);
+    gate_scores();
+    grams();
+  } else {
+    Records rec;
+    setup(rec);
+    __syncthreads();
+    if (s_misc[0] != SLA_OK) return;
+    if (a.has_pending) stage_records(rec);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    stage_second_tile();
   }
-  // the gathered records have landed (the staged state rows may still be in flight)
-  if (w == kSetup) __builtin_amdgcn_s_waitcnt(waitcnt_vm(L::kPreInstr));
   __syncthreads();
+  plen = s_misc[1];
 
   if (DELTA && w == kSetup) {
     // ---- the diagonal blocks of T = (I + Lk)^-1, less the identity, in place
@@ -741,17 +868,24 @@ void verify_tile_kernel(VerifyArgs a) {
 #pragma unroll
     for (int mt = 0; mt < NT; ++mt) pq[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 rreg[NT];
-    if (cols_live) {
-      const int ps = plen < kPMax ? plen : kPMax;
-      const AT *pkg = static_cast<const AT *>(a.pend.k);
-      const int pn = a.has_pending ? a.pend.n : 1;
-      if (a.has_pending) {
+    // delayed state update, kPMax steps of the accepted path at a time; longer
+    // paths restage the records between two barriers (plen is
+    // workgroup-uniform).  (Each column wave used to read the steps past the
+    // first eight itself, two dependent reads per step.)
+    for (int c0 = 0; c0 < plen; c0 += kPMax) {
+      if (c0 + (plen > kPMax ? i : 0) > 0) {
+        __syncthreads();
+        if (w == kSetup) restage_records(c0, i);
+        __syncthreads();
+      }
+      const int ps = plen - c0 < kPMax ? plen - c0 : kPMax;
+      if (cols_live) {
         // the whole tile has normally landed by now: step-major, one LDS
         // round trip per step
         for (int st = 0; st < ps; ++st) {
           const float al = s_palpha[st];
           const float uv = pu[st * kTileCols + ucol];
-          constexpr int KC = KS < 2 ? KS : 2;  // K-steps per LDS round trip
+          constexpr int KC = F32 || GV || KS < 4 ? 2 : 4;  // K-steps per LDS round trip
 #pragma unroll
           for (int k0 = 0; k0 < KS; k0 += KC) {
             float kv[KC][8];  // the key's rows 32 (k0 + c) + 8 lg + e
@@ -785,21 +919,10 @@ void verify_tile_kernel(VerifyArgs a) {
                 hf[k0 + c][e] = apply_factor(hf[k0 + c][e], GV ? gv[c][e] : al, kv[c][e], uv);
           }
         }
-        // paths longer than the LDS stage read their records directly
-        for (int st = kPMax; st < plen; ++st) {
-          const int node = a.pend.path[(size_t)b * pn + st];
-          const size_t r = ((size_t)b * pn + node) * H + h;
-          const float al = GV ? 1.f : a.pend.alpha[r];
-          const float uv = a.pend.u[r * dv + col];
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks) {
-            float kr[8], gr[8];
-            load_f32<8>(pkg + r * DK + ks * 32 + 8 * lg, kr);
-            if constexpr (GV) load_f32<8>(a.pend.alpha + r * DK + ks * 32 + 8 * lg, gr);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) hf[ks][e] = apply_factor(hf[ks][e], GV ? gr[e] : al, kr[e], uv);
-          }
-        }
+      }
+    }
+    if (cols_live) {
+      if (a.has_pending) {
         // committed rows back.  A wave writes half of each 128-byte line and
         // the neighbouring wave the other half.  Over many rounds of
         // workgroups the default policy lets the L2 merge the halves (a plain
@@ -1011,46 +1134,40 @@ int device_cus() {
   return cus;
 }
 
-// The state reads of a workgroup normally go out first, so that they overlap
-// the setup wave's dependent reads.  When the launch holds at least
-// kLateRounds rounds of workgroups (resident workgroups per CU from the
-// occupancy of the kernel instantiation), they go out after the first
-// barrier instead: measured 4.5% faster on the 1-node decode chain at batch
-// 256, 1% slower at one round.  At one to kLateRounds rounds the column waves
-// hold them back briefly instead (stagger).
+// Rounds of workgroups from which a launch is kModeLate.
 constexpr int kLateRounds = 4;
 
 template <int DK, int NP, int CW, int TPW, int KIND, bool F32>
 hipError_t launch_np(const VerifyArgs &a, hipStream_t s) {
   using L = Layout<DK, NP, CW, TPW, KIND, F32>;
-  const size_t lds = L::kBytes;
-  if (lds > kMaxLds) return hipErrorInvalidConfiguration;
-  auto kern_wb = verify_tile_kernel<DK, NP, CW, TPW, KIND, F32, false>;  // committed rows written back
-  auto kern_wt = verify_tile_kernel<DK, NP, CW, TPW, KIND, F32, true>;   // written through
-  if (lds > kDefaultLds) {
-    for (auto k : {kern_wb, kern_wt}) {
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-    }
+  constexpr size_t lds = L::kBytes;
+  if constexpr (lds > kMaxLds) {
+    return hipErrorInvalidConfiguration;
+  } else {
+    using Kernel = void (*)(VerifyArgs);
+    const Kernel part = verify_tile_kernel<DK, NP, CW, TPW, KIND, F32, kModePart>;
+    const Kernel round = verify_tile_kernel<DK, NP, CW, TPW, KIND, F32, kModeRound>;
+    const Kernel late = verify_tile_kernel<DK, NP, CW, TPW, KIND, F32, kModeLate>;
+    auto allow_lds = [](Kernel k) {
+      if (lds <= kDefaultLds) return hipSuccess;
+      return hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    };
+    // resident workgroups per CU for this instantiation (registers, LDS, waves)
+    static const int per_cu = [&] {
+      int k = 0;
+      if (allow_lds(round) != hipSuccess ||
+          hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, round, kWaves<CW> * kWave, lds) != hipSuccess || k < 1) k = 1;
+      return k;
+    }();
+    const int ntiles = (a.dv + L::kTileCols - 1) / L::kTileCols;
+    const size_t groups = (size_t)a.B * a.H * ((ntiles + TPW - 1) / TPW);
+    const size_t slots = (size_t)per_cu * device_cus();
+    const Kernel kern = groups >= (size_t)kLateRounds * slots ? late : (groups >= slots && a.dv % 32 == 0 ? round : part);
+    const hipError_t e = allow_lds(kern);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kWaves<CW> * kWave), lds, s, a);
+    return hipGetLastError();
   }
-  const int ntiles = (a.dv + L::kTileCols - 1) / L::kTileCols;
-  const size_t groups = (size_t)a.B * a.H * ((ntiles + TPW - 1) / TPW);
-  VerifyArgs b = a;
-  // resident workgroups per CU for this instantiation (registers, LDS, waves)
-  static const int per_cu = [&] {
-    int k = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, kern_wb, kWaves<CW> * kWave, lds) != hipSuccess || k < 1) k = 1;
-    return k;
-  }();
-  const size_t slots = (size_t)per_cu * device_cus();
-  b.late_state = groups >= (size_t)kLateRounds * slots;
-  b.stagger = !b.late_state && groups >= slots;
-  // write-through only for a full round of workgroups that all stay resident:
-  // below a round the launch is latency-bound and the writes' completion
-  // lengthens it (batch 1, 32 workgroups: 8.6 -> 9.9 us per round)
-  hipLaunchKernelGGL(b.stagger ? kern_wt : kern_wb, dim3((unsigned)groups), dim3(kWaves<CW> * kWave), lds, s, b);
-  return hipGetLastError();
 }
 
 template <int DK, int KIND, bool F32>
