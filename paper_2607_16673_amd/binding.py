@@ -1,10 +1,12 @@
-"""Thin ctypes binding of libsla (C ABI in include/sla.h).
+"""Thin binding of libsla (C ABI in include/sla.h).
 
 Argument marshalling only: torch tensors are checked for device, dtype,
 shape and contiguity, turned into raw device pointers plus the current HIP
-stream, and passed to the library.  Every step of the verification and
-commit runs in the library's HIP kernels; there is no fallback of any kind.
-If ``libsla.so`` has not been built, every call raises.
+stream, and passed to the library (the device calls of a serving step in the
+native module ``_native``, the rest through ctypes).  Every step of the
+verification and commit runs in the library's HIP kernels; there is no
+fallback of any kind.  If the libraries have not been built, every call
+raises.
 """
 from __future__ import annotations
 
@@ -129,6 +131,23 @@ def lib():
     return _lib
 
 
+_nat = None
+
+
+def native():
+    """The marshalling module of the device calls; raises if it has not been built."""
+    global _nat
+    if _nat is None:
+        lib()
+        _torch()  # its libraries, before the module's
+        try:
+            from . import _native
+        except ModuleNotFoundError as e:
+            raise RuntimeError("_native.so is not built (run `python -m paper_2607_16673_amd.build`)") from e
+        _nat = _native
+    return _nat
+
+
 def status_string(code: int) -> str:
     return lib().sla_status_string(int(code)).decode()
 
@@ -180,15 +199,6 @@ def _torch():
     return torch
 
 
-def _dtype_code(t) -> int:
-    torch = _torch()
-    if t.dtype == torch.bfloat16:
-        return SLA_DTYPE_BF16
-    if t.dtype == torch.float32:
-        return SLA_DTYPE_F32
-    raise TypeError("q/k/v must be bfloat16 or float32, got %s" % t.dtype)
-
-
 def _dev(t, dtype, shape, name):
     torch = _torch()
     if not isinstance(t, torch.Tensor):
@@ -224,13 +234,6 @@ class Factors:
                        torch.empty(gate_shape(batch, n, heads, d_k, family), dtype=torch.float32, device=device),
                        torch.empty(batch, n, dtype=torch.int32, device=device))
 
-    def c(self, dtype, B, n, H, dk, dv, family="gdn") -> SlaFactors:
-        torch = _torch()
-        return SlaFactors(_dev(self.k, dtype, (B, n, H, dk), "factors.k"),
-                          _dev(self.u, torch.float32, (B, n, H, dv), "factors.u"),
-                          _dev(self.alpha, torch.float32, gate_shape(B, n, H, dk, family), "factors.alpha"),
-                          _dev(self.parent, torch.int32, (B, n), "factors.parent"))
-
 
 def _check(code, what):
     if code != SLA_OK:
@@ -246,43 +249,21 @@ def sla_verify(state, q, k, v, alpha, beta, parent_idx, out, factors: Factors, *
     "deltanet"); beta: [B][n][H] fp32 (None for "decay" and "gla").
     pending: None or (factors_prev: Factors, path [B][n_prev] int32, len [B] int32).
     Raises SlaError on a host-detected error."""
-    torch = _torch()
-    B, n, H, dk = q.shape
-    dv = v.shape[-1]
-    dt = _dtype_code(q)
-    shape = SlaShape(B, H, dk, dv, n, dt, TOPOLOGIES[topology], FAMILIES[family], ROUTES[route])
-    f = factors.c(q.dtype, B, n, H, dk, dv, family)
-    pend_p = None
     if pending is not None:
-        pf, ppath, plen = pending
-        pn = pf.parent.shape[1]
-        pend = SlaPending(pf.c(q.dtype, B, pn, H, dk, dv, family), pn,
-                          _dev(ppath, torch.int32, (B, pn), "pending.path"),
-                          _dev(plen, torch.int32, (B,), "pending.len"))
-        pend_p = ctypes.byref(pend)
-    st_p = _dev(status, torch.int32, (B,), "status") if status is not None else None
-    code = lib().sla_verify(
-        ctypes.byref(shape), _dev(state, torch.float32, (B, H, dk, dv), "state"), pend_p,
-        _dev(q, q.dtype, (B, n, H, dk), "q"), _dev(k, q.dtype, (B, n, H, dk), "k"),
-        _dev(v, q.dtype, (B, n, H, dv), "v"),
-        _dev(alpha, torch.float32, gate_shape(B, n, H, dk, family), "alpha") if alpha is not None else None,
-        _dev(beta, torch.float32, (B, n, H), "beta") if beta is not None else None,
-        _dev(parent_idx, torch.int32, (B, n), "parent_idx"),
-        _dev(out, torch.float32, (B, n, H, dv), "out"), ctypes.byref(f), st_p, _stream(q.device))
+        pf, path, length = pending
+        pk, pu, pa, pp = pf.k, pf.u, pf.alpha, pf.parent
+    else:
+        pk = pu = pa = pp = path = length = None
+    code = (_nat or native()).verify(state, q, k, v, alpha, beta, parent_idx, out, factors.k, factors.u, factors.alpha,
+                                     factors.parent, pk, pu, pa, pp, path, length, status, TOPOLOGIES[topology],
+                                     FAMILIES[family], ROUTES[route])
     _check(code, "sla_verify")
 
 
 def sla_commit(state, factors: Factors, path, length, *, status=None, family: str = "gdn"):
     """Enqueue an immediate commit of the accepted paths (see sla_commit)."""
-    torch = _torch()
-    B, n, H, dk = factors.k.shape
-    dv = factors.u.shape[-1]
-    shape = SlaShape(B, H, dk, dv, n, _dtype_code(factors.k), SLA_TOPO_TREE, FAMILIES[family], SLA_ROUTE_AUTO)
-    f = factors.c(factors.k.dtype, B, n, H, dk, dv, family)
-    st_p = _dev(status, torch.int32, (B,), "status") if status is not None else None
-    code = lib().sla_commit(ctypes.byref(shape), _dev(state, torch.float32, (B, H, dk, dv), "state"),
-                            ctypes.byref(f), _dev(path, torch.int32, (B, n), "path"),
-                            _dev(length, torch.int32, (B,), "len"), st_p, _stream(state.device))
+    code = (_nat or native()).commit(state, factors.k, factors.u, factors.alpha, factors.parent, path, length, status,
+                                     FAMILIES[family])
     _check(code, "sla_commit")
 
 
@@ -320,44 +301,16 @@ def sla_conv_verify(conv_state, x, weight, parent_idx, y, *, bias=None, pending:
     [D][K] fp32; bias [D] fp32 or None; parent_idx [B][n] int32.
     pending: None or (x_prev [B][n_prev][D], parent_prev [B][n_prev], path
     [B][n_prev] int32, len [B] int32).  Raises SlaError on a host-detected error."""
-    torch = _torch()
-    B, n, D = x.shape
-    K = weight.shape[1]
-    shape = make_conv_shape(B, D, K, n, "bf16" if x.dtype == torch.bfloat16 else "f32", activation)
-    _dtype_code(x)
-    cs = _dev(conv_state, torch.float32, (B, K - 1, D), "conv_state") if conv_state is not None else None
-    pend_p = None
-    if pending is not None:
-        px, ppar, ppath, plen = pending
-        pn = ppar.shape[1]
-        pend = SlaConvPending(_dev(px, x.dtype, (B, pn, D), "pending.x"),
-                              _dev(ppar, torch.int32, (B, pn), "pending.parent"), pn,
-                              _dev(ppath, torch.int32, (B, pn), "pending.path"),
-                              _dev(plen, torch.int32, (B,), "pending.len"))
-        pend_p = ctypes.byref(pend)
-    bias_p = _dev(bias, torch.float32, (D,), "bias") if bias is not None else None
-    st_p = _dev(status, torch.int32, (B,), "status") if status is not None else None
-    code = lib().sla_conv_verify(ctypes.byref(shape), cs, pend_p, _dev(x, x.dtype, (B, n, D), "x"),
-                                 _dev(weight, torch.float32, (D, K), "weight"), bias_p,
-                                 _dev(parent_idx, torch.int32, (B, n), "parent_idx"),
-                                 _dev(y, x.dtype, (B, n, D), "y"), st_p, _stream(x.device))
+    px, pparent, path, length = pending if pending is not None else (None, None, None, None)
+    code = (_nat or native()).conv_verify(conv_state, x, weight, parent_idx, y, bias, px, pparent, path, length, status,
+                                          activation)
     _check(code, "sla_conv_verify")
 
 
 def sla_conv_commit(conv_state, x, parent_idx, path, length, *, kernel_size=None, status=None):
     """Enqueue an immediate conv-state commit of the accepted paths (see
     sla_conv_commit).  conv_state [B][K-1][D] fp32 (None when K = 1)."""
-    torch = _torch()
-    B, n, D = x.shape
-    K = kernel_size if kernel_size is not None else conv_state.shape[1] + 1
-    shape = make_conv_shape(B, D, K, n, "bf16" if x.dtype == torch.bfloat16 else "f32")
-    _dtype_code(x)
-    cs = _dev(conv_state, torch.float32, (B, K - 1, D), "conv_state") if conv_state is not None else None
-    st_p = _dev(status, torch.int32, (B,), "status") if status is not None else None
-    code = lib().sla_conv_commit(ctypes.byref(shape), cs, _dev(x, x.dtype, (B, n, D), "x"),
-                                 _dev(parent_idx, torch.int32, (B, n), "parent_idx"),
-                                 _dev(path, torch.int32, (B, n), "path"),
-                                 _dev(length, torch.int32, (B,), "len"), st_p, _stream(x.device))
+    code = (_nat or native()).conv_commit(conv_state, x, parent_idx, path, length, kernel_size, status)
     _check(code, "sla_conv_commit")
 
 
@@ -382,19 +335,7 @@ def sla_prune(parent, logp, tau: float, budget: int = 0, *, with_scores: bool = 
     sla_prune).  parent [B][n] int32, logp [B][n] fp32 (device tensors).
     Returns dict of device tensors: packed_parent, index_map, count, status
     (and scores)."""
-    torch = _torch()
-    B, n = parent.shape
-    dev = parent.device
-    pp = torch.empty(B, n, dtype=torch.int32, device=dev)
-    im = torch.empty(B, n, dtype=torch.int32, device=dev)
-    cnt = torch.empty(B, dtype=torch.int32, device=dev)
-    st = torch.empty(B, dtype=torch.int32, device=dev)
-    sc = torch.empty(B, n, dtype=torch.float32, device=dev) if with_scores else None
-    code = lib().sla_prune(_dev(parent, torch.int32, (B, n), "parent"), _dev(logp, torch.float32, (B, n), "logp"),
-                           B, n, float(tau), int(budget), _dev(pp, None, None, "packed_parent"),
-                           _dev(im, None, None, "index_map"), _dev(cnt, None, None, "count"),
-                           _dev(sc, None, None, "scores") if sc is not None else None,
-                           _dev(st, None, None, "status"), _stream(dev))
+    code, pp, im, cnt, st, sc = (_nat or native()).prune(parent, logp, float(tau), int(budget), with_scores)
     _check(code, "sla_prune")
     out = dict(packed_parent=pp, index_map=im, count=cnt, status=st)
     if sc is not None:

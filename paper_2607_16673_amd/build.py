@@ -3,11 +3,15 @@ include/sla.h) in-tree, next to this file.
 
 Every HIP translation unit is compiled by hipcc for gfx950 only, with packed
 fp32 instructions disabled (the library relies on ordinary fp32 VALU and
-matrix-core arithmetic), then linked into one shared library.
+matrix-core arithmetic), then linked into one shared library.  The Python
+binding's marshalling module (_native) is host code linked against it and
+against torch.
 """
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -16,6 +20,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsla.so")
+NATIVE = os.path.join(HERE, "_native.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
@@ -48,15 +53,45 @@ def _compile(unit, verbose: bool) -> str:
     return obj
 
 
+def _compile_native(verbose: bool) -> str:
+    """The marshalling module's object file (host code only)."""
+    # torch's place without importing it
+    torch = os.path.dirname(importlib.util.find_spec("torch").origin)
+    obj = os.path.join(BUILD, "torch_binding.o")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-I" + INCLUDE, "-isystem" + os.path.join(torch, "include"), "-isystem/opt/rocm/include",
+           "-isystem" + sysconfig.get_paths()["include"], "-Wall", "-Wno-unused-result",
+           "-c", os.path.join(CSRC, "torch_binding.cpp"), "-o", obj]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for torch_binding.cpp:\n" + r.stdout + r.stderr)
+    return obj
+
+
+def _link_native(obj: str, verbose: bool) -> None:
+    torch = os.path.join(os.path.dirname(importlib.util.find_spec("torch").origin), "lib")
+    cmd = ["g++", "-shared", "-fPIC", "-o", NATIVE + ".tmp", obj, "-L" + HERE, "-l:libsla.so", "-L" + torch, "-ltorch_python",
+           "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + torch]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(NATIVE + ".tmp", NATIVE)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        native = ex.submit(_compile_native, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
+        native = native.result()
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", LIB + ".tmp"] + objs
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(LIB + ".tmp", LIB)
+    _link_native(native, verbose)
     return LIB
 
 
