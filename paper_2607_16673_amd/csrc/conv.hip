@@ -9,19 +9,19 @@
 // inputs into C; fused in front of a verification it is the delayed update
 // of §5.2 applied to C.
 //
-// One workgroup = one sequence b and a chunk of 512 channels, 8 per lane,
-// with up to four waves (eight above 32 nodes) that split the draft's nodes.
-// Each wave first reads
-// the parent row into lanes (lane j holds node j), then issues its share of
-// the chunk's draft rows straight into LDS (global_load_lds_dwordx4: 16
-// bytes per lane, one instruction per bf16 row, two per fp32 row), and the
-// weights into registers.  Topology and path checks are wave shuffles.  The
-// accepted rows are gathered (at most K - 1 of them, whatever the path
-// length) and the committed rows written back.  After one barrier every
-// node's window is read from LDS by ancestor index: K fused multiply-adds
-// per channel, SiLU, one 16-byte store per lane.  Wave 0 alone reads the
-// conv state, checks topology and path, gathers the accepted rows and writes
-// the committed rows back; the others read them from LDS.
+// One workgroup = one sequence b and a chunk of channels, 8 per lane (512 of
+// them in large launches, 128 or 64 in small ones), with two to eight waves
+// that split the draft's nodes.  Each wave first reads the parent row into
+// lanes (lane j holds node j).  Wave 0 takes the dependent reads alone: the
+// path, the conv state and, once the path is known, at most K - 1 accepted
+// rows (whatever the path length); it writes the committed rows back and puts
+// them in LDS.  The other waves bring the chunk's draft rows and weights
+// straight into LDS (global_load_lds_dwordx4).  Topology and path checks are
+// wave shuffles.  After one barrier every node's window is read from LDS by
+// ancestor index: K fused multiply-adds per channel, SiLU, one 16-byte store
+// per lane.  (With wave 0 reading rows as well, its path check waited for
+// them: one sequence of 32 nodes took 8.9 us, now 4.1; 64-node trees at batch
+// 256 137 us, now 117.)
 // A 1-node draft (the decode step) takes a single wave that reads its row
 // and the conv state straight into registers (conv_node_kernel).
 // The bound is HBM: the draft rows and outputs stream once, the conv state
@@ -178,56 +178,46 @@ __device__ __forceinline__ void window_sources(int p, int lane, int (&src)[K]) {
   }
 }
 
-template <typename XT, int K>
+// CL: lanes (of 8 channels) per row of the chunk; a wave covers 64 / CL rows.
+// Wave 0 takes the chain of dependent reads alone (path, then the accepted
+// rows); the other waves bring the draft rows and the weights, so neither
+// waits for the other's reads.
+template <typename XT, int K, int CL>
 __global__ __launch_bounds__(kConvWaves * kWave) void conv_verify_kernel(ConvArgs a) {
   constexpr int P = kPieces<XT>;
   constexpr int KR = K > 1 ? K - 1 : 1;
+  constexpr int RW = kWave / CL;  // rows per wave
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  const int w = threadIdx.x / kWave;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int l = threadIdx.x % kWave;
+  const int g = l % CL, rsub = l / CL;
   const int nw = blockDim.x / kWave;
-  const int nchunks = (a.D + kChunk - 1) / kChunk;
+  const int nchunks = (a.D + CL * kCpl - 1) / (CL * kCpl);
   const int b = blockIdx.x / nchunks;
-  const int c0raw = (blockIdx.x % nchunks) * kChunk + l * kCpl;
+  const int c0raw = (blockIdx.x % nchunks) * (CL * kCpl) + g * kCpl;
   const bool live = c0raw < a.D;
   const int c0 = live ? c0raw : a.D - kCpl;  // lanes past the last channel re-read the last 8
   const int n = a.n;
-  // LDS: draft rows [n][P][64 lanes x 16 B], then the committed rows
-  // [K-1][2][64 x 16 B] (fp32, 8 channels per lane), then the verdict
-  f32x4 *crows = reinterpret_cast<f32x4 *>(lds + (size_t)n * P * kWave * 16);
-  int *s_err = reinterpret_cast<int *>(crows + KR * 2 * kWave);
-  // with several waves: [2K pieces][64 lanes], lane l's weights, 16 bytes per piece
-  f32x4 *wrows = reinterpret_cast<f32x4 *>(s_err + 4);
+  const int NR = (n + RW - 1) / RW * RW;  // staged rows
+  // LDS, in 16-byte pieces: draft rows [P][NR][CL], committed rows [K-1][2][CL]
+  // (fp32, 8 channels per lane), weights [2K][CL] (a lane's 8 K floats are
+  // contiguous in [D][K]; piece-major, so that reads are conflict-free), verdict
+  u32x4 *rows = reinterpret_cast<u32x4 *>(lds);
+  f32x4 *crows = reinterpret_cast<f32x4 *>(rows + (size_t)P * NR * CL);
+  f32x4 *wrows = crows + KR * 2 * CL;
+  int *s_err = reinterpret_cast<int *>(wrows + (2 * K * CL + kWave - 1) / kWave * kWave);
 
-  // every wave: the parent row (lane j: node j), then its share of the draft
-  // rows (j = w, w + nw, ...) straight into LDS
   const int p = l < n ? a.parent[(size_t)b * n + l] : -1;
-  int pv = -2, pa = -1, plen = 0;
-  const int pn = a.has_pending ? a.pend_n : 1;
-  if (w == 0 && a.has_pending) {  // wave 0 also takes the pending path
-    pv = l < pn ? a.pend_parent[(size_t)b * pn + l] : -2;
-    pa = l < pn ? a.path[(size_t)b * pn + l] : -1;
-    plen = a.len[b];
-  }
-  const XT *x = static_cast<const XT *>(a.x) + (size_t)b * n * a.D;
-  for (int j = w; j < n; j += nw)
-#pragma unroll
-    for (int q = 0; q < P; ++q)
-      load_lds16(reinterpret_cast<const unsigned char *>(x + (size_t)j * a.D + c0) + 16 * q,
-                 lds + (size_t)(j * P + q) * (kWave * 16));
-  // with several waves, the chunk's weights once per workgroup (a lane's 8 K
-  // floats are contiguous in [D][K]): piece v of every lane in one
-  // instruction, laid out [v][lane] so that the reads after the barrier are
-  // conflict-free.  A single wave reads its own straight into registers.
-  const bool wshared = nw > 1;
-  if (wshared)
-    for (int v = w; v < 2 * K; v += nw) load_lds16(a.weight + (size_t)c0 * K + 4 * v, wrows + v * kWave);
-  int src[K];
-  window_sources<K>(p, l, src);
-
-  // wave 0: topology, the pending path, the committed rows (at most K - 1
-  // accepted rows gathered) into LDS and, with a pending path, back to HBM
   if (w == 0) {
+    // topology, the pending path, the committed rows (at most K - 1 accepted
+    // rows gathered) into LDS and, with a pending path, back to HBM
+    const int pn = a.has_pending ? a.pend_n : 1;
+    int pv = -2, pa = -1, plen = 0;
+    if (a.has_pending) {
+      pv = l < pn ? a.pend_parent[(size_t)b * pn + l] : -2;
+      pa = l < pn ? a.path[(size_t)b * pn + l] : -1;
+      plen = a.len[b];
+    }
     float cs[KR][kCpl];
     float *crow = K > 1 ? a.conv_state + (size_t)b * (K - 1) * a.D + c0 : nullptr;
     if constexpr (K > 1) {
@@ -247,7 +237,7 @@ __global__ __launch_bounds__(kConvWaves * kWave) void conv_verify_kernel(ConvArg
         commit_rows<XT, K>(cs, static_cast<const XT *>(a.pend_x) + (size_t)b * pn * a.D, (size_t)a.D, plen, node,
                            c0);
         if constexpr (K > 1) {
-          if (live) {
+          if (live && l < CL) {
 #pragma unroll
             for (int r = 0; r < K - 1; ++r) store_f8(crow + (size_t)r * a.D, cs[r]);
           }
@@ -255,14 +245,30 @@ __global__ __launch_bounds__(kConvWaves * kWave) void conv_verify_kernel(ConvArg
       }
     }
     if constexpr (K > 1) {
+      if (l < CL) {
 #pragma unroll
-      for (int r = 0; r < K - 1; ++r) {
-        crows[(2 * r) * kWave + l] = f32x4{cs[r][0], cs[r][1], cs[r][2], cs[r][3]};
-        crows[(2 * r + 1) * kWave + l] = f32x4{cs[r][4], cs[r][5], cs[r][6], cs[r][7]};
+        for (int r = 0; r < K - 1; ++r) {
+          crows[(2 * r) * CL + l] = f32x4{cs[r][0], cs[r][1], cs[r][2], cs[r][3]};
+          crows[(2 * r + 1) * CL + l] = f32x4{cs[r][4], cs[r][5], cs[r][6], cs[r][7]};
+        }
       }
     }
     if (l == 0) *s_err = err;
     if (a.status && l == 0 && blockIdx.x % nchunks == 0) a.status[b] = err;
+  } else {
+    // a wave instruction brings 64 consecutive pieces: RW rows of one piece
+    // plane, or 64 / CL weight pieces (padding re-reads the last row or piece)
+    const XT *x = static_cast<const XT *>(a.x) + (size_t)b * n * a.D + c0;
+    const int nrj = P * NR / RW;
+    for (int i = w - 1; i < nrj; i += nw - 1) {
+      const int rp = i * RW + rsub, q = rp / NR, row = rp % NR;
+      load_lds16(reinterpret_cast<const unsigned char *>(x + (size_t)(row < n ? row : n - 1) * a.D) + 16 * q,
+                 rows + (size_t)i * kWave);
+    }
+    for (int i = w - 1; i * RW < 2 * K; i += nw - 1) {
+      const int v = i * RW + rsub;
+      load_lds16(a.weight + (size_t)c0 * K + 4 * (v < 2 * K ? v : 2 * K - 1), wrows + i * kWave);
+    }
   }
   float bias[kCpl];
   if (a.bias) {
@@ -271,16 +277,17 @@ __global__ __launch_bounds__(kConvWaves * kWave) void conv_verify_kernel(ConvArg
 #pragma unroll
     for (int e = 0; e < kCpl; ++e) bias[e] = 0.f;
   }
+  int src[K];
+  window_sources<K>(p, l, src);
   __builtin_amdgcn_s_waitcnt(0);  // this wave's rows and weight pieces have landed
   __syncthreads();                // and every other wave's, and the committed rows
   if (*s_err != SLA_OK) return;
   float wt[K][kCpl];
   {
     float flat[K * kCpl];
-    const f32x4 *wv = reinterpret_cast<const f32x4 *>(a.weight + (size_t)c0 * K);
 #pragma unroll
     for (int v = 0; v < 2 * K; ++v) {
-      const f32x4 t = wshared ? wrows[v * kWave + l] : wv[v];
+      const f32x4 t = wrows[v * CL + g];
       flat[4 * v] = t.x; flat[4 * v + 1] = t.y; flat[4 * v + 2] = t.z; flat[4 * v + 3] = t.w;
     }
 #pragma unroll
@@ -290,23 +297,23 @@ __global__ __launch_bounds__(kConvWaves * kWave) void conv_verify_kernel(ConvArg
   }
 
   XT *y = static_cast<XT *>(a.y) + (size_t)b * n * a.D + c0;
-  const u32x4 *rows = reinterpret_cast<const u32x4 *>(lds) + l;
-  for (int j = w; j < n; j += nw) {
+  for (int j0 = w * RW; j0 < n; j0 += nw * RW) {  // wave-uniform: the lane reads below need every lane
+    const int jr = j0 + rsub, j = jr < n ? jr : n - 1;
     float acc[kCpl];
 #pragma unroll
     for (int e = 0; e < kCpl; ++e) acc[e] = bias[e];
 #pragma unroll
     for (int s = 0; s < K; ++s) {
-      const int sj = __builtin_amdgcn_readlane(src[s], j);  // lag s of node j
+      const int sj = RW == 1 ? __builtin_amdgcn_readlane(src[s], j) : __shfl(src[s], j);  // lag s of node j
       float z[kCpl];
       if (sj >= 0) {
         u32x4 r[P];
 #pragma unroll
-        for (int q = 0; q < P; ++q) r[q] = rows[(sj * P + q) * kWave];
+        for (int q = 0; q < P; ++q) r[q] = rows[(q * NR + sj) * CL + g];
         widen(r, z, XT{});
       } else {
         const int rr = -sj - 1;  // committed row
-        const f32x4 lo = crows[(2 * rr) * kWave + l], hi = crows[(2 * rr + 1) * kWave + l];
+        const f32x4 lo = crows[(2 * rr) * CL + g], hi = crows[(2 * rr + 1) * CL + g];
         z[0] = lo.x; z[1] = lo.y; z[2] = lo.z; z[3] = lo.w;
         z[4] = hi.x; z[5] = hi.y; z[6] = hi.z; z[7] = hi.w;
       }
@@ -318,7 +325,7 @@ __global__ __launch_bounds__(kConvWaves * kWave) void conv_verify_kernel(ConvArg
 #pragma unroll
       for (int e = 0; e < kCpl; ++e) acc[e] = silu(acc[e]);
     }
-    if (live) store_row(y + (size_t)j * a.D, acc);
+    if (live && jr < n) store_row(y + (size_t)j * a.D, acc);
   }
 }
 
@@ -462,6 +469,28 @@ __global__ __launch_bounds__(kWave) void conv_commit_kernel(ConvArgs a) {
   }
 }
 
+template <typename XT, int K, int CL>
+hipError_t launch_verify(const ConvArgs &a, hipStream_t s) {
+  constexpr int RW = kWave / CL;
+  const int NR = (a.n + RW - 1) / RW * RW, K1 = K > 1 ? K - 1 : 1;
+  const size_t groups = (size_t)a.B * ((a.D + CL * kCpl - 1) / (CL * kCpl));
+  // The waves split the draft's nodes: eight for drafts of more than 32 nodes
+  // (64-node trees at batch 256: 117 us; 143 us with four that all read rows),
+  // else four, and a fifth where each then has several rows left (batch 64, 16
+  // nodes: 10.9 -> 10.5 us; with four nodes 11.4 -> 14.2 us).
+  const int most = a.n > 32 ? kConvWaves : (CL == kWave && a.n > 8 ? 5 : 4), need = NR / RW;
+  const int waves = need < 2 ? 2 : (need < most ? need : most);
+  const size_t lds = ((size_t)kPieces<XT> * NR * CL + (size_t)K1 * 2 * CL + (size_t)(2 * K * CL + kWave - 1) / kWave * kWave) * 16 + 16;
+  auto kern = conv_verify_kernel<XT, K, CL>;
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(waves * kWave), lds, s, a);
+  return hipGetLastError();
+}
+
 template <typename XT, int K>
 hipError_t launch_k(const ConvArgs &a, bool commit, hipStream_t s) {
   const int nchunks = (a.D + kChunk - 1) / kChunk;
@@ -474,22 +503,17 @@ hipError_t launch_k(const ConvArgs &a, bool commit, hipStream_t s) {
     hipLaunchKernelGGL((conv_node_kernel<XT, K>), grid, dim3(kWave), 0, s, a);
     return hipGetLastError();
   }
-  const int K1 = K > 1 ? K - 1 : 1;
-  // the waves split the draft's nodes: eight for drafts of more than 32 nodes,
-  // else up to four (measured at batch 256, 64-node trees: 157 -> 143 us per
-  // launch with eight; at batch 64, 16-node trees eight were 25% slower); with
-  // several, the chunk's weights are staged in LDS once
-  const int waves = a.n > 32 ? kConvWaves : (a.n < 4 ? a.n : 4);
-  const size_t lds = (size_t)a.n * kPieces<XT> * kWave * 16 + (size_t)K1 * 2 * kWave * 16 + 16 +
-                     (waves > 1 ? (size_t)2 * K * kWave * 16 : 0);
-  auto kern = conv_verify_kernel<XT, K>;
-  if (lds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(kern, grid, dim3(waves * kWave), lds, s, a);
-  return hipGetLastError();
+  // Lanes per row by the workgroups that 512-channel chunks would make:
+  // narrower chunks put small batches on more CUs (measured us per launch with
+  // 64, 32, 16 and 8 lanes, bf16, K 4, 6144 channels: batch 1, 32 nodes 7.77,
+  // 6.17, 4.81, 4.13; batch 4, 16 nodes 5.92, 5.19, 4.55, 4.75; batch 16 6.58,
+  // 6.37, 5.88, 6.32; batch 32, 8 nodes 6.34, 6.09, 6.42, 8.15; batch 64, 48
+  // nodes, 4096 channels 14.2, 16.6, 21.2, 31.6; 32 lanes gain too little to be
+  // kept as a form of their own)
+  const size_t wide = (size_t)a.B * ((a.D + kChunk - 1) / kChunk);
+  if (wide < 32) return launch_verify<XT, K, 8>(a, s);
+  if (wide <= 256) return launch_verify<XT, K, 16>(a, s);
+  return launch_verify<XT, K, 64>(a, s);
 }
 
 template <typename XT>
