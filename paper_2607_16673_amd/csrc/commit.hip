@@ -17,7 +17,7 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int kCommitThreads = 256;
 constexpr int kCommitCols = 64;   // state columns per workgroup
-constexpr int kCommitStage = 8;   // path records staged in LDS; longer paths read the rest directly
+constexpr int kCommitStage = 8;   // path records staged in LDS at a time
 
 // One workgroup = one (b, h) unit's 64-column slab, all d_k rows (the slabs
 // of a unit numbered back to back on one XCD in full launches).  Thread t
@@ -25,8 +25,10 @@ constexpr int kCommitStage = 8;   // path records staged in LDS; longer paths re
 // 256-byte row segment, so every access is whole 128-byte lines.  The slab
 // is read first thing, before the path is known; wave 0 reads the path, the
 // parent row and the gates whole (validation takes no dependent read), then
-// gathers the records the path names straight into LDS.  An invalid path
-// reports its status and leaves the state untouched.
+// gathers the records the path names straight into LDS, eight at a time (64
+// chains of 32 nodes, 16 heads, d_v 128: 99 us with the records past the
+// eighth read by every thread, 31 us restaged).  An invalid path reports its
+// status and leaves the state untouched.
 // VG: the records hold d_k gates each (GLA), staged like the key rows.
 template <typename T, int DK, bool VG>
 __global__ __launch_bounds__(kCommitThreads) void commit_kernel(CommitArgs a) {
@@ -38,7 +40,7 @@ __global__ __launch_bounds__(kCommitThreads) void commit_kernel(CommitArgs a) {
   __shared__ __attribute__((aligned(16))) float s_g[VG ? kCommitStage * DK : 4];  // [kCommitStage][DK]
   const T *s_k = reinterpret_cast<const T *>(s_kraw);  // [kCommitStage][DK]
   const int tid = threadIdx.x;
-  const int w = tid / kWave, l = tid % kWave;
+  const int w = __builtin_amdgcn_readfirstlane(tid / kWave), l = tid % kWave;
   const int H = a.H, dv = a.dv, n = a.n;
   const int nslab = (dv + kCommitCols - 1) / kCommitCols;
   size_t uid;
@@ -78,24 +80,13 @@ __global__ __launch_bounds__(kCommitThreads) void commit_kernel(CommitArgs a) {
       for (int r = 0; r < R; ++r) x[r] = buf_load_f4<kPolicyDefault>(sr, vo, (uint32_t)(16 * r * dv) * 4);
     }
   }
-  if (w == 0) {
-    // step t is node path[t], whose parent must be path[t - 1] (-1 for t = 0)
-    const bool inrange = node >= 0 && node < n;
-    const int nodec = inrange ? node : 0;
-    int prev = __shfl_up(node, 1);
-    if (l == 0) prev = -1;
-    const int pp = __shfl(par, nodec);
-    const float pa = __shfl(al, nodec);
-    const bool bad = (len < 0 || len > n) || (l < len && (!inrange || pp != prev));
-    const int err = wave_any(bad) ? SLA_ERR_PATH : SLA_OK;
-    if (l == 0) {
-      s_err = err;
-      s_len = len;
-    }
-    if (l < kCommitStage) s_alpha[l] = pa;
-    if (h == 0 && slab == 0 && l == 0 && a.status) a.status[b] = err;
-    // records of the first steps (indices clamped into the store): key rows
-    // and this slab's corrected values, straight into LDS
+  // wave 0: the records of steps c0 .. c0 + kCommitStage - 1 (indices clamped
+  // into the store): key rows, gates and this slab's corrected values, straight
+  // into LDS
+  int nodec = 0;   // wave 0, lane t: node of step t
+  float pa = 0.f;  // and its gate
+  auto stage = [&](int c0) {
+    if (l >= c0 && l < c0 + kCommitStage) s_alpha[l - c0] = pa;
     const T *fk = static_cast<const T *>(a.k);
     constexpr int KC = DK * (int)sizeof(T) / 16;  // 16-byte chunks per key row
     constexpr int KI = kCommitStage * KC / kWave;
@@ -103,9 +94,9 @@ __global__ __launch_bounds__(kCommitThreads) void commit_kernel(CommitArgs a) {
     constexpr int GI = VG ? kCommitStage * GC / kWave : 0;
     int nt[KI], ng[GI > 0 ? GI : 1];  // shuffles first: an LDS instruction after an LDS-DMA load waits for it
 #pragma unroll
-    for (int i = 0; i < KI; ++i) nt[i] = __shfl(nodec, (i * kWave + l) / KC);
+    for (int i = 0; i < KI; ++i) nt[i] = __shfl(nodec, c0 + (i * kWave + l) / KC);
 #pragma unroll
-    for (int i = 0; i < GI; ++i) ng[i] = __shfl(nodec, (i * kWave + l) / GC);
+    for (int i = 0; i < GI; ++i) ng[i] = __shfl(nodec, c0 + (i * kWave + l) / GC);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < KI; ++i)
@@ -115,41 +106,57 @@ __global__ __launch_bounds__(kCommitThreads) void commit_kernel(CommitArgs a) {
       load_lds16(a.alpha + ((rowp + ng[i]) * H + h) * DK + ((i * kWave + l) % GC) * 4, s_g + i * kWave * 4);
 #pragma unroll
     for (int t = 0; t < kCommitStage; ++t) {
-      const int ntt = __builtin_amdgcn_readlane(nodec, t);
+      const int ntt = __builtin_amdgcn_readlane(nodec, c0 + t);
       const int c = slab * kCommitCols + l;
       load_lds4(a.u + ((rowp + ntt) * H + h) * dv + (c < dv ? c : dv - 1), &s_u[t][0]);
     }
     __builtin_amdgcn_s_waitcnt(0);  // the records have landed
+  };
+  if (w == 0) {
+    // step t is node path[t], whose parent must be path[t - 1] (-1 for t = 0)
+    const bool inrange = node >= 0 && node < n;
+    nodec = inrange ? node : 0;
+    int prev = __shfl_up(node, 1);
+    if (l == 0) prev = -1;
+    const int pp = __shfl(par, nodec);
+    pa = __shfl(al, nodec);
+    const bool bad = (len < 0 || len > n) || (l < len && (!inrange || pp != prev));
+    const int err = wave_any(bad) ? SLA_ERR_PATH : SLA_OK;
+    if (l == 0) {
+      s_err = err;
+      s_len = len;
+    }
+    if (h == 0 && slab == 0 && l == 0 && a.status) a.status[b] = err;
+    stage(0);
   }
   __syncthreads();
-  if (s_err != SLA_OK || !cl) return;
+  if (s_err != SLA_OK) return;
   len = s_len;
   const int cs = (tid % 16) * 4;  // column within the slab
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i = tid / 16 + 16 * r;
-    for (int t = 0; t < len && t < kCommitStage; ++t) {
-      const float alt = VG ? s_g[t * DK + i] : s_alpha[t];
-      const float ki = to_f32(s_k[t * DK + i]);
+  auto apply = [&](int steps) {
+    for (int t = 0; t < steps; ++t) {  // step by step: one read of u for all rows
       const float4 u = *reinterpret_cast<const float4 *>(&s_u[t][cs]);
-      x[r].x = apply_factor(x[r].x, alt, ki, u.x);
-      x[r].y = apply_factor(x[r].y, alt, ki, u.y);
-      x[r].z = apply_factor(x[r].z, alt, ki, u.z);
-      x[r].w = apply_factor(x[r].w, alt, ki, u.w);
+      const float al = VG ? 0.f : s_alpha[t];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int i = tid / 16 + 16 * r;
+        const float alt = VG ? s_g[t * DK + i] : al;
+        const float ki = to_f32(s_k[t * DK + i]);
+        x[r].x = apply_factor(x[r].x, alt, ki, u.x);
+        x[r].y = apply_factor(x[r].y, alt, ki, u.y);
+        x[r].z = apply_factor(x[r].z, alt, ki, u.z);
+        x[r].w = apply_factor(x[r].w, alt, ki, u.w);
+      }
     }
-    // paths longer than the stage read their records directly
-    for (int t = kCommitStage; t < len; ++t) {
-      const size_t s = (rowp + a.path[rowp + t]) * H + h;
-      const float alt = VG ? a.alpha[s * DK + i] : a.alpha[s];
-      const float ki = to_f32(static_cast<const T *>(a.k)[s * DK + i]);
-      const float4 u = *reinterpret_cast<const float4 *>(a.u + s * dv + cg);
-      x[r].x = apply_factor(x[r].x, alt, ki, u.x);
-      x[r].y = apply_factor(x[r].y, alt, ki, u.y);
-      x[r].z = apply_factor(x[r].z, alt, ki, u.z);
-      x[r].w = apply_factor(x[r].w, alt, ki, u.w);
-    }
+  };
+  apply(len < kCommitStage ? len : kCommitStage);
+  for (int c0 = kCommitStage; c0 < len; c0 += kCommitStage) {  // len is workgroup-uniform
+    __syncthreads();
+    if (w == 0) stage(c0);
+    __syncthreads();
+    apply(len - c0 < kCommitStage ? len - c0 : kCommitStage);
   }
-  if (len == 0) return;
+  if (len == 0 || !cl) return;
   // whole lines; with a workgroup per CU or more, written through at device
   // scope, so that nothing is left dirty in the L2 for the end of the kernel
   // (measured against plain stores: the separate route at batched tree

@@ -187,10 +187,13 @@ constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) 
 
 // Waves per SIMD the register allocation is held to: 6 (80 VGPRs) where the
 // tile state, accumulators and LDS allow a fourth resident workgroup per CU;
-// 4 (128 VGPRs) for the eight-wave form, so that two workgroups fit a CU;
-// else whatever the allocation needs.
-template <int DK, int NP, int CW, bool F32>
-constexpr int kMinWaves = F32 ? 1 : ((DK <= 128 && NP <= 16) ? 6 : (CW == 8 ? 4 : 1));
+// 4 (128 VGPRs) for the eight-wave form where its LDS lets two workgroups fit
+// a CU; else whatever the allocation needs.
+constexpr size_t kMaxLds = 160 * 1024;
+constexpr size_t kDefaultLds = 64 * 1024;
+template <int DK, int NP, int CW, int TPW, int KIND, bool F32>
+constexpr int kMinWaves =
+    F32 ? 1 : ((DK <= 128 && NP <= 16) ? 6 : (CW == 8 && 2 * Layout<DK, NP, CW, TPW, KIND, F32>::kBytes <= kMaxLds ? 4 : 1));
 
 // KIND: the family's form (see Layout).  Without the delta rule Lk = 0, so
 // T = I and U = R = V: no P_k, no Lk, no T.
@@ -203,7 +206,7 @@ constexpr int kWaves = CW == 8 ? CW : CW + 1;
 
 // MODE: how a launch's rounds of workgroups order the state reads (kMode*).
 template <int DK, int NP, int CW, int TPW, int KIND, bool F32, int MODE>
-__global__ __launch_bounds__(kWaves<CW> * kWave) __attribute__((amdgpu_waves_per_eu(kMinWaves<DK, NP, CW, F32>)))
+__global__ __launch_bounds__(kWaves<CW> * kWave) __attribute__((amdgpu_waves_per_eu(kMinWaves<DK, NP, CW, TPW, KIND, F32>)))
 void verify_tile_kernel(VerifyArgs a) {
   using L = Layout<DK, NP, CW, TPW, KIND, F32>;
   using AT = std::conditional_t<F32, float, bf16>;  // activation element
@@ -1123,8 +1126,6 @@ void verify_tile_kernel(VerifyArgs a) {
   if constexpr (TPW == 2) step(1, hfb, hfa);
 }
 
-constexpr size_t kMaxLds = 160 * 1024;
-constexpr size_t kDefaultLds = 64 * 1024;
 
 int device_cus() {
   int dev = 0, cus = 0;
@@ -1170,6 +1171,32 @@ hipError_t launch_np(const VerifyArgs &a, hipStream_t s) {
   }
 }
 
+// Drafts of more than 16 nodes: single 64-column tiles while they do not fill
+// the CUs (one, or two where two stages fit a CU's LDS); else one workgroup
+// covers more columns, so that topology, Grams and the inverse serve them all
+// and, where one stage fills a CU, eight column waves instead of four share it.
+// Measured, us per launch: 64 nodes, 16 heads, d_k 128, d_v 256, single tiles
+// against pairs of 128 columns: batch 1 12.6 and 22.2, batch 4 16.1 and 24.3,
+// batch 8 (512 tiles) 21.7 and 26.0, batch 16 45.9 and 30.9; 8 heads, d_k = d_v
+// = 256, 64 nodes: batch 4 19.4 and 32.8, batch 32 80.3 and 55.5 (one tile of
+// 128 columns: 57.5); 16 heads, d_k 256, d_v 128, batch 16: 42.3, and 28.4 in
+// one tile of 128 columns.
+template <int DK, int NP, int KIND, bool F32>
+hipError_t launch_large(const VerifyArgs &a, hipStream_t s) {
+  constexpr size_t stage = Layout<DK, NP, 4, 1, KIND, F32>::kBytes;
+  constexpr size_t fit = kMaxLds / stage < 2 ? 1 : 2;
+  const size_t tiles = (size_t)a.B * a.H * ((a.dv + kWaveCols * 4 - 1) / (kWaveCols * 4));
+  if ((NP > 32 || fit == 1) && tiles > fit * device_cus()) {
+    if (a.dv % 256 == 0) return launch_np<DK, NP, 8, 2, KIND, F32>(a, s);
+    if constexpr (fit == 1) {
+      if (a.dv % 128 == 0) return launch_np<DK, NP, 8, 1, KIND, F32>(a, s);
+    } else if (((a.dv + kWaveCols * 4 - 1) / (kWaveCols * 4)) % 2 == 0) {
+      return launch_np<DK, NP, 4, 2, KIND, F32>(a, s);
+    }
+  }
+  return launch_np<DK, NP, 4, 1, KIND, F32>(a, s);
+}
+
 template <int DK, int KIND, bool F32>
 hipError_t launch_dk(const VerifyArgs &a, hipStream_t s) {
   // small trees: two V-tiles of a unit per workgroup once single tiles would
@@ -1183,16 +1210,7 @@ hipError_t launch_dk(const VerifyArgs &a, hipStream_t s) {
       return a.n <= 16 ? launch_np<DK, 16, 4, 2, KIND, F32>(a, s) : launch_np<DK, 32, 4, 2, KIND, F32>(a, s);
   }
   if (a.n <= 16) return launch_np<DK, 16, 4, 1, KIND, F32>(a, s);
-  if (a.n <= 32) return launch_np<DK, 32, 4, 1, KIND, F32>(a, s);
-  // large trees: two V-tiles per workgroup -- topology, Grams and T serve
-  // both, and the second tile's state loads overlap the first tile's U, O
-  // and stores; with d_v a multiple of 256, tiles of 128 columns (eight
-  // column waves), so that one workgroup covers 256 columns
-  if constexpr (DK <= 128) {
-    if (a.dv % 256 == 0) return launch_np<DK, 64, 8, 2, KIND, F32>(a, s);
-    if (((a.dv + kWaveCols * 4 - 1) / (kWaveCols * 4)) % 2 == 0) return launch_np<DK, 64, 4, 2, KIND, F32>(a, s);
-  }
-  return launch_np<DK, 64, 4, 1, KIND, F32>(a, s);
+  return a.n <= 32 ? launch_large<DK, 32, KIND, F32>(a, s) : launch_large<DK, 64, KIND, F32>(a, s);
 }
 
 }  // namespace
