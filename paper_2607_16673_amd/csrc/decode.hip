@@ -34,7 +34,7 @@ constexpr int kCols = 64;   // state columns per workgroup
 constexpr int kStage = 8;   // path records staged in LDS; longer paths read the rest directly
 
 template <typename T, int DK, bool VG>
-__global__ __launch_bounds__(kThreads) void decode_kernel(VerifyArgs a) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 5))) void decode_kernel(VerifyArgs a) {
   constexpr int R = DK / 16;  // rows per thread
   __shared__ int s_err, s_len;
   __shared__ float s_alpha[kStage];
@@ -161,23 +161,29 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(VerifyArgs a) {
   // delayed update: the accepted records, root first, then the write-back
   if (len > 0) {
     const int cs = (tid % 16) * 4;
+    for (int t = 0; t < len && t < kStage; ++t) {  // step by step: one read of u for all rows
+      const float4 u = *reinterpret_cast<const float4 *>(&s_u[t][cs]);
+      const float al0 = VG ? 0.f : s_alpha[t];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int i = tid / 16 + 16 * r;
-      for (int t = 0; t < len && t < kStage; ++t) {
-        const float alt = VG ? s_g[t * DK + i] : s_alpha[t];
+      for (int r = 0; r < R; ++r) {
+        const int i = tid / 16 + 16 * r;
+        const float alt = VG ? s_g[t * DK + i] : al0;
         const float ki = to_f32(s_k[t * DK + i]);
-        const float4 u = *reinterpret_cast<const float4 *>(&s_u[t][cs]);
         x[r].x = apply_factor(x[r].x, alt, ki, u.x);
         x[r].y = apply_factor(x[r].y, alt, ki, u.y);
         x[r].z = apply_factor(x[r].z, alt, ki, u.z);
         x[r].w = apply_factor(x[r].w, alt, ki, u.w);
       }
-      for (int t = kStage; t < len; ++t) {
-        const size_t s = (rowp + a.pend.path[rowp + t]) * H + h;
-        const float alt = VG ? a.pend.alpha[s * DK + i] : a.pend.alpha[s];
+    }
+    for (int t = kStage; t < len; ++t) {
+      const size_t s = (rowp + a.pend.path[rowp + t]) * H + h;
+      const float4 u = *reinterpret_cast<const float4 *>(a.pend.u + s * dv + cgc);
+      const float al0 = VG ? 0.f : a.pend.alpha[s];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int i = tid / 16 + 16 * r;
+        const float alt = VG ? a.pend.alpha[s * DK + i] : al0;
         const float ki = to_f32(static_cast<const T *>(a.pend.k)[s * DK + i]);
-        const float4 u = *reinterpret_cast<const float4 *>(a.pend.u + s * dv + cgc);
         x[r].x = apply_factor(x[r].x, alt, ki, u.x);
         x[r].y = apply_factor(x[r].y, alt, ki, u.y);
         x[r].z = apply_factor(x[r].z, alt, ki, u.z);

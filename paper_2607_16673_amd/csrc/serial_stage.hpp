@@ -26,29 +26,37 @@ __host__ __device__ inline size_t serial_stage_bytes(int n, int dk, bool vg) {
          sizeof(int) * (4 * n) + sizeof(uint64_t) * n;
 }
 
-template <int DK, bool VG>
+// The stage of SL > 1 V-tiles of one unit that share the draft: one array of
+// values and corrected values per tile (a node's value is read once, right
+// before its corrected value takes its place).
+__host__ __device__ inline size_t shared_stage_bytes(int n, int dk, bool vg, int sl) {
+  return sizeof(float) * ((size_t)(vg ? 3 : 2) * n * dk + (size_t)sl * n * kSliceCols + 2 * n) + sizeof(int) * (4 * n) +
+         sizeof(uint64_t) * n;
+}
+
+template <int DK, bool VG, int SL = 1>
 __device__ inline SerialStage carve_stage(float *lds, int n) {
   SerialStage s;
   s.ks = lds;
   s.qs = s.ks + n * DK;
   s.gs = s.qs + n * DK;
   s.vs = s.gs + (VG ? n * DK : 0);
-  s.us = s.vs + n * kSliceCols;
-  s.als = s.us + n * kSliceCols;
+  s.us = SL > 1 ? s.vs : s.vs + n * kSliceCols;
+  s.als = s.us + SL * n * kSliceCols;
   s.bes = s.als + n;
   s.ia = reinterpret_cast<int *>(s.bes + n);
   s.ib = s.ia + n;
   s.ic = s.ib + n;
   s.id = s.ic + n;
-  s.ancs = reinterpret_cast<uint64_t *>(s.id + n);  // 4 n (c DK + 34) + 16 n bytes in (c = 2 or 3): 8-byte aligned
+  s.ancs = reinterpret_cast<uint64_t *>(s.id + n);  // a multiple of 8 n bytes in: 8-byte aligned
   return s;
 }
 
 // Stage the unit's draft with `nthr` threads (thread `t`): keys, queries and
-// gates as fp32 rows, the values of V-tile `tile`, alpha and beta; with
-// `records`, also write the factor records that do not depend on the V-tile
+// gates as fp32 rows, the values of V-tiles `tile` .. tile + SL - 1 (those past
+// the last re-read it), alpha and beta; with `records`, also write the factor records that do not depend on the V-tile
 // (the key as given and the gate; the parent array when h == 0).
-template <int DK, typename T, bool VG>
+template <int DK, typename T, bool VG, int SL = 1>
 __device__ inline void stage_draft(const VerifyArgs &a, const SerialStage &s, int b, int h, int tile, int t,
                                    int nthr, bool delta, bool records) {
   const int H = a.H, dv = a.dv, n = a.n;
@@ -76,9 +84,11 @@ __device__ inline void stage_draft(const VerifyArgs &a, const SerialStage &s, in
       gd[1] = make_float4(gv[4], gv[5], gv[6], gv[7]);
     }
   }
-  for (int idx = t; idx < n * kSliceCols; idx += nthr) {
-    const int j = idx / kSliceCols, cc = idx % kSliceCols;
-    s.vs[idx] = to_f32(v[(((size_t)b * n + j) * H + h) * dv + tile * kSliceCols + cc]);
+  for (int idx = t; idx < SL * n * kSliceCols; idx += nthr) {
+    const int jj = idx / kSliceCols, cc = idx % kSliceCols;
+    const int sl = jj / n, j = jj % n;
+    const int col = (tile + sl) * kSliceCols + cc;
+    s.vs[idx] = to_f32(v[(((size_t)b * n + j) * H + h) * dv + (SL == 1 || col < dv ? col : dv - 1)]);
   }
   for (int j = t; j < n; j += nthr) {
     const size_t sj = ((size_t)b * n + j) * H + h;
@@ -107,14 +117,17 @@ __device__ inline void stage_draft(const VerifyArgs &a, const SerialStage &s, in
 }
 
 // The delayed state update of one lane's rows: the pending path's records
-// applied to H (rows row0 .. row0 + R - 1 of column col), root first.
+// applied to H (rows row0 .. row0 + R - 1 of column col), root first.  Lane t
+// holds step t's node (one read of the path, not one per step).
 template <int DK, int R, typename T, bool VG>
 __device__ inline void apply_pending(const VerifyArgs &a, int b, int h, int col, int row0, int plen,
                                      float (&H)[R]) {
   const T *pk = static_cast<const T *>(a.pend.k);
   const int pn = a.pend.n, Hn = a.H, dv = a.dv;
+  const int lane = threadIdx.x % kWave;
+  const int nodes = a.pend.path[(size_t)b * pn + (lane < pn ? lane : pn - 1)];
   for (int t = 0; t < plen; ++t) {
-    const int node = a.pend.path[(size_t)b * pn + t];
+    const int node = __builtin_amdgcn_readlane(nodes, t);
     const size_t s = ((size_t)b * pn + node) * Hn + h;
     const float u = a.pend.u[s * dv + col];
     float kr[R], gr[R];

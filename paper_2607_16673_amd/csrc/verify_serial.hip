@@ -158,24 +158,40 @@ __global__ __launch_bounds__(kWave) void verify_serial_kernel(VerifyArgs a) {
 // ---------------------------------------------------------------- hybrid
 constexpr int kMaxLevels = 8;  // light edges on a root path <= log2(64) = 6
 
-// LDS beyond the stage: heavy-child keys and heavy children [n], per-level
+// LDS beyond the stage: light leaf children [n] (64-bit masks), per-level
 // chain-head lists [kMaxLevels][n], per-level counts, the error code and the
-// deepest level.
+// deepest level.  (The heavy-child keys and children lie in the stage.)
 __host__ __device__ inline size_t hybrid_extra_bytes(int n) {
   return sizeof(int) * (2 * n + kMaxLevels * n + kMaxLevels + 2);
 }
 
-template <int DK, typename T, bool VG, int W>
-__global__ __launch_bounds__(W * kWave) void verify_hybrid_kernel(VerifyArgs a) {
+// SL > 1: a workgroup takes SL neighbouring V-tiles of a unit, W waves each, on
+// one staged draft.  At d_k = 256 the stage of a large draft fills a CU's LDS,
+// so with one tile per workgroup a CU ran four waves, one per SIMD, and staged
+// the draft anew for every 16 columns (8 sequences, 8 heads, d_k = d_v = 256,
+// 64 fp32 nodes: 260 us).
+template <int DK, typename T, bool VG, int W, int SL>
+__global__ __launch_bounds__(W * SL * kWave) void verify_hybrid_kernel(VerifyArgs a) {
   constexpr int R = DK / kGroups;
   const int tid = threadIdx.x;
-  const int w = tid / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int sl = wave % SL;  // this wave's tile of the workgroup's
+  const int w = wave / SL;   // and its place among that tile's waves
   const int lane = tid % kWave;
   const int c = lane & (kCols - 1);
   const int g = lane / kCols;
   const int n = a.n;
-  int tile, b, h;
-  if (!slice_of(a, tile, b, h)) return;  // the whole workgroup: no barrier follows
+  int tile0, b, h;
+  if constexpr (SL == 1) {
+    if (!slice_of(a, tile0, b, h)) return;  // the whole workgroup: no barrier follows
+  } else {
+    const int ng = (a.dv / kCols + SL - 1) / SL;
+    tile0 = (int)(blockIdx.x % ng) * SL;
+    h = (int)(blockIdx.x / ng % a.H);
+    b = (int)(blockIdx.x / ng / a.H);
+  }
+  const bool live = (tile0 + sl) * kCols < a.dv;  // wave-uniform; the others only take the barriers
+  const int tile = live ? tile0 + sl : a.dv / kCols - 1;
   const int col = tile * kCols + c;
   const int row0 = g * R;
   const size_t unit = (size_t)b * a.H + h;
@@ -189,22 +205,23 @@ __global__ __launch_bounds__(W * kWave) void verify_hybrid_kernel(VerifyArgs a) 
   for (int r = 0; r < R; ++r) H0[r] = st[(size_t)(row0 + r) * a.dv];
 
   extern __shared__ __attribute__((aligned(16))) float lds[];
-  const SerialStage s = carve_stage<DK, VG>(lds, n);
+  SerialStage s = carve_stage<DK, VG, SL>(lds, n);
   int *hkey = s.ia;       // [n] heavy-child key: (subtree size << 7) | (127 - child)
   int *heavy = s.ib;      // [n] heavy child, -1 for a leaf
-  int *lists = reinterpret_cast<int *>(lds + serial_stage_bytes(n, DK, VG) / 4);  // [kMaxLevels][n]
+  uint64_t *leaves = s.ancs + n;  // [n] light children without children
+  int *lists = reinterpret_cast<int *>(leaves + n);  // [kMaxLevels][n]
   int *counts = lists + kMaxLevels * n;   // [kMaxLevels]
   int *misc = counts + kMaxLevels;        // error code, deepest level
 
   // ---- wave 0: topology, pending-path check, heavy-light decomposition
-  if (w == 0) {
+  if (wave == 0) {
     NodeTopo topo;
     int err = build_topology(a.parent + (size_t)b * n, n, lane, false, topo);
     if (err == SLA_OK && a.has_pending) {
       err = check_path(a.pend.parent + (size_t)b * a.pend.n, a.pend.n, a.pend.path + (size_t)b * a.pend.n,
                        a.pend.len[b], lane);
     }
-    if (tile == 0 && h == 0 && lane == 0 && a.status) a.status[b] = err;
+    if (tile0 == 0 && h == 0 && lane == 0 && a.status) a.status[b] = err;
     if (lane == 0) misc[0] = err;
     if (err == SLA_OK) {
       const bool live = lane < n;
@@ -218,6 +235,15 @@ __global__ __launch_bounds__(W * kWave) void verify_hybrid_kernel(VerifyArgs a) 
       const int ph = __shfl(hv, topo.parent >= 0 ? topo.parent : 0);
       const bool head = live && (topo.parent < 0 || ph != lane);
       const uint64_t heads = __ballot(head);
+      // with few waves per tile, light leaf children are verified from the
+      // state their parent's chain has on chip (a node's outputs need its
+      // parent's state only), not as chains of their own that rebuild it
+      const bool leaf_child = SL > 1 && head && topo.parent >= 0 && topo.n_children == 0;
+      const uint64_t leaf_children = __ballot(leaf_child);
+      uint64_t mine = 0;
+      for (int i = 0; i < n; ++i)
+        mine |= ((leaf_children >> i) & 1ull) && __builtin_amdgcn_readlane(topo.parent, i) == lane ? 1ull << i : 0ull;
+      const uint64_t starts = heads & ~leaf_children;  // the chains
       // level: chain starts strictly above this node's chain head
       const int lvl = live ? __popcll(topo.anc & heads) - 1 : 0;
       const int hd = live ? 63 - __builtin_clzll(topo.anc & heads) : -1;  // this node's chain head
@@ -226,7 +252,7 @@ __global__ __launch_bounds__(W * kWave) void verify_hybrid_kernel(VerifyArgs a) 
       // rank within the level: longer chains first, then smaller head index
       int rank = 0;
       for (int i = 0; i < n; ++i) {
-        const uint64_t hi = heads >> i;
+        const uint64_t hi = starts >> i;
         if (!(hi & 1ull)) continue;  // wave-uniform
         const int li = __builtin_amdgcn_readlane(lvl, i);
         const int ni = __builtin_amdgcn_readlane(len, i);
@@ -235,17 +261,19 @@ __global__ __launch_bounds__(W * kWave) void verify_hybrid_kernel(VerifyArgs a) 
       int cnt = 0;  // lane L < kMaxLevels: chains at level L
       for (int i = 0; i < n; ++i) {
         const int li = __builtin_amdgcn_readlane(lvl, i);
-        cnt += ((heads >> i) & 1ull) && li == lane;
+        cnt += ((starts >> i) & 1ull) && li == lane;
       }
-      int deepest = head ? lvl : 0;
+      const bool start = head && !leaf_child;
+      int deepest = start ? lvl : 0;
       for (int o = 1; o < kWave; o <<= 1) deepest = max(deepest, __shfl_xor(deepest, o));
       if (live) {
         heavy[lane] = hv;
+        leaves[lane] = mine;
         s.ancs[lane] = topo.anc;
       }
       // (heavy-light: a chain start at least halves the subtree, so a 64-node
       // draft has at most 6 levels above level 0; the tables hold 8)
-      if (head && lvl < kMaxLevels) lists[lvl * n + rank] = lane;
+      if (start && lvl < kMaxLevels) lists[lvl * n + rank] = lane;
       if (lane < kMaxLevels) counts[lane] = cnt;
       if (lane == 0) misc[1] = min(deepest, kMaxLevels - 1);
     }
@@ -255,10 +283,12 @@ __global__ __launch_bounds__(W * kWave) void verify_hybrid_kernel(VerifyArgs a) 
 
   // ---- every wave: stage the draft, commit the pending path into its copy of
   //      the tile; wave 0 writes the committed tile back
-  stage_draft<DK, T, VG>(a, s, b, h, tile, tid, W * kWave, delta, tile == 0);
+  stage_draft<DK, T, VG, SL>(a, s, b, h, tile0, tid, W * SL * kWave, delta, tile0 == 0);
+  s.vs += sl * n * kCols;  // this wave's tile from here on
+  s.us += sl * n * kCols;
   if (a.has_pending) {
     apply_pending<DK, R, T, VG>(a, b, h, col, row0, a.pend.len[b], H0);
-    if (w == 0) {
+    if (w == 0 && live) {
 #pragma unroll
       for (int r = 0; r < R; ++r) st[(size_t)(row0 + r) * a.dv] = H0[r];
     }
@@ -268,7 +298,7 @@ __global__ __launch_bounds__(W * kWave) void verify_hybrid_kernel(VerifyArgs a) 
   // ---- the chains, level by level; wave w takes ranks w, w + W, ...
   const int deepest = misc[1];
   for (int lvl = 0; lvl <= deepest; ++lvl) {
-    const int cnt = counts[lvl];
+    const int cnt = live ? counts[lvl] : 0;
     for (int r = w; r < cnt; r += W) {
       const int head = lists[lvl * n + r];
       // boundary state: the committed tile advanced by the head's ancestors
@@ -285,6 +315,11 @@ __global__ __launch_bounds__(W * kWave) void verify_hybrid_kernel(VerifyArgs a) 
         const float u = node_step<DK, R, VG>(a, s, Hc, j, b, h, c, g, row0, col, delta);
         const int nx = heavy[j];
         if (nx >= 0) advance<DK, R, VG>(s, Hc, j, row0, u);
+        uint64_t lm = readlane_u64(leaves[j], 0);  // wave-uniform; none without a heavy child
+        while (lm) {
+          node_step<DK, R, VG>(a, s, Hc, __builtin_ctzll(lm), b, h, c, g, row0, col, delta);
+          lm &= lm - 1;
+        }
         j = nx;
       }
     }
@@ -341,19 +376,42 @@ hipError_t launch_t(const VerifyArgs &a, hipStream_t s) {
 
 // Waves per workgroup: four up to 16 nodes and at d_k = 256 (two copies of a
 // 256-row slice take most of a wave's registers), else eight.
-template <int DK, typename T, int W>
+template <int DK, typename T, int W, int SL = 1>
 hipError_t launch_hybrid_w(const VerifyArgs &a, hipStream_t s) {
-  const dim3 grid = slice_grid(a);
   const bool vg = a.family == SLA_FAMILY_GLA;
-  const size_t lds = serial_stage_bytes(a.n, DK, vg) + hybrid_extra_bytes(a.n);
-  const dim3 block(W * kWave);
-  if (vg) return launch_with_lds(verify_hybrid_kernel<DK, T, true, W>, grid, block, lds, s, a);
-  return launch_with_lds(verify_hybrid_kernel<DK, T, false, W>, grid, block, lds, s, a);
+  const int ng = (a.dv / kCols + SL - 1) / SL;
+  const dim3 grid = SL == 1 ? slice_grid(a) : dim3((unsigned)((size_t)a.B * a.H * ng));
+  const size_t lds = (SL == 1 ? serial_stage_bytes(a.n, DK, vg) : shared_stage_bytes(a.n, DK, vg, SL)) + hybrid_extra_bytes(a.n);
+  const dim3 block(W * SL * kWave);
+  if (vg) return launch_with_lds(verify_hybrid_kernel<DK, T, true, W, SL>, grid, block, lds, s, a);
+  return launch_with_lds(verify_hybrid_kernel<DK, T, false, W, SL>, grid, block, lds, s, a);
+}
+
+int device_cus() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+    return 256;
+  return cus;
 }
 
 template <int DK, typename T>
 hipError_t launch_hybrid_dk(const VerifyArgs &a, hipStream_t s) {
-  if constexpr (DK == 256) return launch_hybrid_w<DK, T, 4>(a, s);
+  if constexpr (DK == 256) {
+    const bool vg = a.family == SLA_FAMILY_GLA;
+    const size_t one = serial_stage_bytes(a.n, DK, vg) + hybrid_extra_bytes(a.n);
+    if (one > kMaxLds) return hipErrorInvalidConfiguration;
+    // one stage per CU: two tiles share it, four once pairs would fill the CUs
+    // more than once (8 heads, d_v 256, fp32, one, two and four tiles: 64 nodes
+    // at batch 8 261, --, 104 us; 48 nodes at batch 4 (512 tiles) 106, 64, -- us)
+    const size_t slices = (size_t)a.B * a.H * (a.dv / kCols), cus = device_cus();
+    if (2 * one > kMaxLds) {
+      auto fits = [&](int sl) { return shared_stage_bytes(a.n, DK, vg, sl) + hybrid_extra_bytes(a.n) <= kMaxLds; };
+      if (slices > 2 * cus && a.dv / kCols > 2 && fits(4)) return launch_hybrid_w<DK, T, 2, 4>(a, s);
+      if (a.dv / kCols > 1 && fits(2)) return launch_hybrid_w<DK, T, 4, 2>(a, s);
+    }
+    return launch_hybrid_w<DK, T, 4>(a, s);
+  }
   return a.n <= 16 ? launch_hybrid_w<DK, T, 4>(a, s) : launch_hybrid_w<DK, T, 8>(a, s);
 }
 
