@@ -21,10 +21,11 @@
 // One workgroup = one (batch b, head h) unit's V-tile of CW x 16 columns
 // (CW = 4 or 8), or TPW = 2 consecutive such tiles, with CW + 1 wavefronts
 // (CW = 4) or CW (CW = 8, where column wave 0 also takes the setup work):
-//   waves 0 .. CW-1 own 16 state columns each.  They issue the state tile
-//              reads (in the B-fragment order of v_mfma_f32_16x16x32_bf16: 8
-//              consecutive rows of one column per 32-row K-step) and the
-//              value reads first thing.  The state reads and the
+//   waves 0 .. CW-1 own 16 state columns each.  They bring [Q; K] (a share
+//              each, through registers into LDS), then, held back briefly, the
+//              state tile (in the B-fragment order of
+//              v_mfma_f32_16x16x32_bf16: 8 consecutive rows of one column per
+//              32-row K-step) and the values.  The state reads and the
 //              committed-row writes keep the default cache policy: a wave
 //              covers only half of each 128-byte line, and with a streaming
 //              hint the L2 lets the line go before the neighbouring wave
@@ -38,18 +39,16 @@
 //              and the outputs.  With two tiles, the second tile's reads go
 //              out once the first tile's registers are free.
 //   wave CW    (the setup wave; wave 0 at CW = 8) owns no state of its own.
-//              It takes every read that depends on another read or that
-//              everything else waits for: parent row and gates -> topology,
-//              decays and compact-list offsets; the pending path with the
-//              previous round's parent row and gates -> validation; [Q; K] by
-//              direct global->LDS loads; then, while the column waves
-//              compute, the factor records the path names (also straight
-//              into LDS, a second stage for a second tile) and, for two
-//              16-node tiles with scalar gates, the second tile's first d_k/2
-//              state rows, which would otherwise queue behind the first
-//              tile's work (measured at batch 64, 16 heads, d_v 128: 37.8 ->
-//              36.9 us per launch).  After the Grams it inverts the diagonal
-//              blocks of T.
+//              It takes every read that depends on another read: parent row
+//              and gates -> topology and decays; the pending path with the
+//              previous round's parent row and gates -> validation and, at
+//              once, the factor records the path names (registers, then LDS
+//              while the Grams run; a second stage for a second tile); and,
+//              for two 16-node tiles with scalar gates, the second tile's
+//              first d_k/2 state rows straight into LDS, which would otherwise
+//              queue behind the first tile's work (measured at batch 64, 16
+//              heads, d_v 128: 37.8 -> 36.9 us per launch).  After the Grams
+//              it inverts the diagonal blocks of T.
 // The tree-masked Grams ([Q; K] K^T tiles that hold ancestor pairs, exact
 // bf16 products) run on the column waves; they and T are done while the
 // first tile's state is still in flight.  Strided global accesses go through
@@ -197,10 +196,10 @@ constexpr int kMinWaves =
 
 // KIND: the family's form (see Layout).  Without the delta rule Lk = 0, so
 // T = I and U = R = V: no P_k, no Lk, no T.
-// eight column waves: column wave 0 also does the setup work, so that the
+// Eight column waves: column wave 0 also does the setup work, so that the
 // workgroup is eight waves and two fit a CU at 124 VGPRs (a ninth wave keeps
-// it to one: measured on 64-node trees at batch 64, d_v 256, 459 -> 448 us per
-// launch; its state reads then go out after its record gathers)
+// it to one: measured on 64-node trees at batch 256, d_v 256, 459 -> 448 us per
+// launch; its state reads then go out after its record reads).
 template <int CW>
 constexpr int kWaves = CW == 8 ? CW : CW + 1;
 
