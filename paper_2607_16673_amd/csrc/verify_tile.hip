@@ -119,7 +119,8 @@ struct Layout {
   static constexpr int kT = kDelta ? NB * kBlk : 0;   // -Lk blocks, the diagonal ones inverted in place
   static constexpr int kAt = NB * kBlk;             // Attn blocks
   static constexpr int kPk = kPMax * DK * ES;       // pending keys (activation dtype)
-  static constexpr int kPu = TPW * kPMax * kTileCols * 4;  // pending corrected values, one stage per tile
+  static constexpr int kPuPitch = kTileCols < kWave ? kWave : kTileCols;  // a direct load fills whole waves
+  static constexpr int kPu = TPW * kPMax * kPuPitch * 4;  // pending corrected values, one stage per tile
   static constexpr int kXL = (kGates && !F32) ? kX / 2 : 0;  // low halves of Q~, same chunk layout
   static constexpr int kG = kGates ? NP * DK * 4 : 0;      // the draft's per-key gates
   static constexpr int kPg = kGates ? kPMax * DK * 4 : 0;  // pending per-key gates
@@ -339,9 +340,10 @@ void verify_tile_kernel(VerifyArgs a) {
   //      to bring [Q; K] by itself, straight into LDS, and every LDS operation
   //      behind it waited.)
   constexpr int kLanes = kColWaves * kWave;
-  constexpr int NQ = 2 * NP * CH / kLanes;           // 16-byte chunks per lane
+  constexpr int kQK = 2 * NP * CH;                   // 16-byte chunks of [Q; K]
+  constexpr int NQ = (kQK + kLanes - 1) / kLanes;    // and per lane
   constexpr int GC = DK / 4;                         // 16-byte chunks per gate row
-  constexpr int NG = GV ? NP * GC / kLanes : 0;
+  constexpr int NG = GV ? (NP * GC + kLanes - 1) / kLanes : 0;
   float hfa[KS][8], hfb[KS][8];  // hfb: the next tile's state (prefetching form only)
   VT vraw[NT][4];  // activation bit patterns, widened where they are used
   auto column_reads = [&]() {
@@ -352,6 +354,7 @@ void verify_tile_kernel(VerifyArgs a) {
     u32x4 qk[NQ], gq[NG > 0 ? NG : 1];
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
+      if (i * kLanes + w * kWave >= kQK) continue;  // wave-uniform (three column waves)
       const int P = i * kLanes + w * kWave + l;
       const int row = P / CH, c = (P % CH) ^ (row & 7);
       const bool isq = i * kLanes + w * kWave < NP * CH;  // wave-uniform: a wave's rows lie in one half
@@ -362,6 +365,7 @@ void verify_tile_kernel(VerifyArgs a) {
       const rsrc_t gr = make_rsrc(a.alpha + (nbase * H + h) * DK, ((uint32_t)(n - 1) * rowb + DK) * 4);
 #pragma unroll
       for (int i = 0; i < NG; ++i) {
+        if (i * kLanes + w * kWave >= NP * GC) continue;
         const int P = i * kLanes + w * kWave + l;
         gq[i] = __builtin_amdgcn_raw_buffer_load_b128(gr, ((uint32_t)(P / GC) * rowb + (P % GC) * 4) * 4, 0, kPolicyDefault);
       }
@@ -377,10 +381,12 @@ void verify_tile_kernel(VerifyArgs a) {
     if constexpr (!kLate && kSetup != 0) load_state(t0, hfa);
     load_values(t0, vraw);
 #pragma unroll
-    for (int i = 0; i < NQ; ++i) reinterpret_cast<u32x4 *>(xs)[i * kLanes + w * kWave + l] = qk[i];
+    for (int i = 0; i < NQ; ++i)
+      if (i * kLanes + w * kWave < kQK) reinterpret_cast<u32x4 *>(xs)[i * kLanes + w * kWave + l] = qk[i];
     if constexpr (GV) {
 #pragma unroll
-      for (int i = 0; i < NG; ++i) reinterpret_cast<u32x4 *>(s_g)[i * kLanes + w * kWave + l] = gq[i];
+      for (int i = 0; i < NG; ++i)
+        if (i * kLanes + w * kWave < NP * GC) reinterpret_cast<u32x4 *>(s_g)[i * kLanes + w * kWave + l] = gq[i];
     }
   };
 
@@ -390,7 +396,7 @@ void verify_tile_kernel(VerifyArgs a) {
   //      the LDS stage
   constexpr int KI = kPMax * CH / kWave;            // 16-byte key chunks per lane
   constexpr int GI = GV ? kPMax * GC / kWave : 0;   // 16-byte gate chunks per lane
-  constexpr int UC = kTileCols / kWave;             // corrected values per lane, step and tile
+  constexpr int UC = L::kPuPitch / kWave;           // corrected values per lane, step and tile
   struct Records {
     u32x4 k[KI];
     float u[TPW][kPMax * UC];
@@ -443,7 +449,7 @@ void verify_tile_kernel(VerifyArgs a) {
 #pragma unroll
       for (int st = 0; st < kPMax; ++st)
 #pragma unroll
-        for (int u = 0; u < UC; ++u) s_pu[(i * kPMax + st) * kTileCols + u * kWave + l] = r.u[i][st * UC + u];
+        for (int u = 0; u < UC; ++u) s_pu[(i * kPMax + st) * L::kPuPitch + u * kWave + l] = r.u[i][st * UC + u];
     gather_gates(0);
   };
   // the records of steps c0 .. c0 + kPMax - 1 for tile t0 + i, straight into
@@ -459,7 +465,7 @@ void verify_tile_kernel(VerifyArgs a) {
 #pragma unroll
     for (int st = 0; st < kPMax; ++st)
 #pragma unroll
-      for (int u = 0; u < UC; ++u) load_lds4(pu0 + u_row(c0, st) + u_col(i, u), s_pu + (i * kPMax + st) * kTileCols + u * kWave);
+      for (int u = 0; u < UC; ++u) load_lds4(pu0 + u_row(c0, st) + u_col(i, u), s_pu + (i * kPMax + st) * L::kPuPitch + u * kWave);
     gather_gates(c0);
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
   };
@@ -862,7 +868,7 @@ void verify_tile_kernel(VerifyArgs a) {
     const bool cols_live = live(t);
     const int col = t * kTileCols + ucol;
     const uint32_t sv = (uint32_t)(8 * lg * dv + col) * 4;
-    const float *pu = s_pu + i * kPMax * kTileCols;
+    const float *pu = s_pu + i * kPMax * L::kPuPitch;
 
     // accumulator layout: lane (lg, lc) holds rows 4 lg .. 4 lg + 3 of each
     // 16-row tile, column lc
@@ -886,7 +892,7 @@ void verify_tile_kernel(VerifyArgs a) {
         // round trip per step
         for (int st = 0; st < ps; ++st) {
           const float al = s_palpha[st];
-          const float uv = pu[st * kTileCols + ucol];
+          const float uv = pu[st * L::kPuPitch + ucol];
           constexpr int KC = F32 || GV || KS < 4 ? 2 : 4;  // K-steps per LDS round trip
 #pragma unroll
           for (int k0 = 0; k0 < KS; k0 += KC) {
@@ -1170,6 +1176,15 @@ hipError_t launch_np(const VerifyArgs &a, hipStream_t s) {
   }
 }
 
+// One V-tile per workgroup: 48 columns instead of 64 where the same number of
+// tiles then covers d_v with fewer waves (d_v 48, 80, 96, 144).
+template <int DK, int NP, int KIND, bool F32>
+hipError_t launch_single(const VerifyArgs &a, hipStream_t s) {
+  const int waves = a.dv / kWaveCols;
+  if (waves % 4 != 0 && (waves + 2) / 3 == (waves + 3) / 4) return launch_np<DK, NP, 3, 1, KIND, F32>(a, s);
+  return launch_np<DK, NP, 4, 1, KIND, F32>(a, s);
+}
+
 // Drafts of more than 16 nodes: single 64-column tiles while they do not fill
 // the CUs (one, or two where two stages fit a CU's LDS); else one workgroup
 // covers more columns, so that topology, Grams and the inverse serve them all
@@ -1193,7 +1208,7 @@ hipError_t launch_large(const VerifyArgs &a, hipStream_t s) {
       return launch_np<DK, NP, 4, 2, KIND, F32>(a, s);
     }
   }
-  return launch_np<DK, NP, 4, 1, KIND, F32>(a, s);
+  return launch_single<DK, NP, KIND, F32>(a, s);
 }
 
 template <int DK, int KIND, bool F32>
@@ -1208,7 +1223,7 @@ hipError_t launch_dk(const VerifyArgs &a, hipStream_t s) {
     if (a.n <= 32 && ntiles % 2 == 0 && (size_t)a.B * a.H * ntiles >= (size_t)8 * device_cus())
       return a.n <= 16 ? launch_np<DK, 16, 4, 2, KIND, F32>(a, s) : launch_np<DK, 32, 4, 2, KIND, F32>(a, s);
   }
-  if (a.n <= 16) return launch_np<DK, 16, 4, 1, KIND, F32>(a, s);
+  if (a.n <= 16) return launch_single<DK, 16, KIND, F32>(a, s);
   return a.n <= 32 ? launch_large<DK, 32, KIND, F32>(a, s) : launch_large<DK, 64, KIND, F32>(a, s);
 }
 
