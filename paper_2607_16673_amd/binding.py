@@ -255,8 +255,8 @@ def sla_verify(state, q, k, v, alpha, beta, parent_idx, out, factors: Factors, *
     else:
         pk = pu = pa = pp = path = length = None
     code = (_nat or native()).verify(state, q, k, v, alpha, beta, parent_idx, out, factors.k, factors.u, factors.alpha,
-                                     factors.parent, pk, pu, pa, pp, path, length, status, TOPOLOGIES[topology],
-                                     FAMILIES[family], ROUTES[route])
+                                     factors.parent, pk, pu, pa, pp, path, length, pending is not None, status,
+                                     TOPOLOGIES[topology], FAMILIES[family], ROUTES[route])
     _check(code, "sla_verify")
 
 
@@ -302,8 +302,8 @@ def sla_conv_verify(conv_state, x, weight, parent_idx, y, *, bias=None, pending:
     pending: None or (x_prev [B][n_prev][D], parent_prev [B][n_prev], path
     [B][n_prev] int32, len [B] int32).  Raises SlaError on a host-detected error."""
     px, pparent, path, length = pending if pending is not None else (None, None, None, None)
-    code = (_nat or native()).conv_verify(conv_state, x, weight, parent_idx, y, bias, px, pparent, path, length, status,
-                                          activation)
+    code = (_nat or native()).conv_verify(conv_state, x, weight, parent_idx, y, bias, px, pparent, path, length,
+                                          pending is not None, status, activation)
     _check(code, "sla_conv_verify")
 
 

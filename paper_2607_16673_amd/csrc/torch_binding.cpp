@@ -67,6 +67,12 @@ long number(PyObject *o) {
   return v;
 }
 
+bool truth(PyObject *o) {
+  const int v = PyObject_IsTrue(o);
+  if (v < 0) throw python_error();
+  return v != 0;
+}
+
 // other Python threads run while the library enqueues (a launch can wait for
 // room in the queue)
 template <typename F>
@@ -94,10 +100,11 @@ sla_factors factors(PyObject *const *o, at::ScalarType act, int64_t B, int64_t n
 }
 
 // verify(state, q, k, v, alpha, beta, parent_idx, out, f.k, f.u, f.alpha, f.parent,
-//        p.k | None, p.u, p.alpha, p.parent, path, len, status, topology, family, route)
+//        p.k, p.u, p.alpha, p.parent, path, len, pending, status, topology, family, route)
+// pending: whether p.k .. len are a pending round's (each is then required)
 PyObject *verify(PyObject *, PyObject *const *o, Py_ssize_t nargs) {
   HANDLE_TH_ERRORS
-  count_args(nargs, 22);
+  count_args(nargs, 23);
   const at::Tensor &q = sized(o[1], 4, "q");
   const at::Tensor &v = tensor(o[3], "v");
   TORCH_CHECK_VALUE(v.dim() > 0, "v has no dimensions");
@@ -110,13 +117,13 @@ PyObject *verify(PyObject *, PyObject *const *o, Py_ssize_t nargs) {
   shape.d_v = (int32_t)dv;
   shape.n_nodes = (int32_t)n;
   shape.qkv_dtype = activation_code(q);
-  shape.topology = (int32_t)number(o[19]);
-  shape.family = (int32_t)number(o[20]);
-  shape.route = (int32_t)number(o[21]);
+  shape.topology = (int32_t)number(o[20]);
+  shape.family = (int32_t)number(o[21]);
+  shape.route = (int32_t)number(o[22]);
   const bool gates = shape.family == SLA_FAMILY_GLA;
   const sla_factors f = factors(o + 8, act, B, n, H, dk, dv, gates);
   sla_pending pend;
-  const bool pending = o[12] != Py_None;
+  const bool pending = truth(o[18]);
   if (pending) {
     const int64_t pn = sized(o[15], 2, "pending parent").size(1);
     pend.f = factors(o + 12, act, B, pn, H, dk, dv, gates);
@@ -124,7 +131,7 @@ PyObject *verify(PyObject *, PyObject *const *o, Py_ssize_t nargs) {
     pend.path = static_cast<const int32_t *>(pointer(o[16], at::kInt, {B, pn}, "pending.path"));
     pend.len = static_cast<const int32_t *>(pointer(o[17], at::kInt, {B}, "pending.len"));
   }
-  int32_t *status = static_cast<int32_t *>(optional_pointer(o[18], at::kInt, {B}, "status"));
+  int32_t *status = static_cast<int32_t *>(optional_pointer(o[19], at::kInt, {B}, "status"));
   float *state = static_cast<float *>(pointer(o[0], at::kFloat, {B, H, dk, dv}, "state"));
   const void *qp = device_pointer(q, act, {B, n, H, dk}, "q");
   const void *kp = pointer(o[2], act, {B, n, H, dk}, "k");
@@ -186,20 +193,18 @@ sla_conv_shape conv_shape(const at::Tensor &x, int64_t K, bool silu) {
 }
 
 // conv_verify(conv_state | None, x, weight, parent_idx, y, bias | None,
-//             px | None, pparent, path, len, status, activation)
+//             px, pparent, path, len, pending, status, activation)
 PyObject *conv_verify(PyObject *, PyObject *const *o, Py_ssize_t nargs) {
   HANDLE_TH_ERRORS
-  count_args(nargs, 12);
+  count_args(nargs, 13);
   const at::Tensor &x = sized(o[1], 3, "x");
   const at::Tensor &weight = sized(o[2], 2, "weight");
   const int64_t B = x.size(0), n = x.size(1), D = x.size(2), K = weight.size(1);
   const at::ScalarType act = x.scalar_type();
-  const int silu = PyObject_IsTrue(o[11]);
-  if (silu < 0) throw python_error();
-  const sla_conv_shape shape = conv_shape(x, K, silu);
+  const sla_conv_shape shape = conv_shape(x, K, truth(o[12]));
   float *cs = static_cast<float *>(optional_pointer(o[0], at::kFloat, {B, K - 1, D}, "conv_state"));
   sla_conv_pending pend;
-  const bool pending = o[6] != Py_None;
+  const bool pending = truth(o[10]);
   if (pending) {
     const int64_t pn = sized(o[7], 2, "pending parent").size(1);
     pend.x = pointer(o[6], act, {B, pn, D}, "pending.x");
@@ -209,7 +214,7 @@ PyObject *conv_verify(PyObject *, PyObject *const *o, Py_ssize_t nargs) {
     pend.len = static_cast<const int32_t *>(pointer(o[9], at::kInt, {B}, "pending.len"));
   }
   const void *bias = optional_pointer(o[5], at::kFloat, {D}, "bias");
-  int32_t *status = static_cast<int32_t *>(optional_pointer(o[10], at::kInt, {B}, "status"));
+  int32_t *status = static_cast<int32_t *>(optional_pointer(o[11], at::kInt, {B}, "status"));
   const void *xp = device_pointer(x, act, {B, n, D}, "x");
   const void *wp = device_pointer(weight, at::kFloat, {D, K}, "weight");
   const void *parent = pointer(o[3], at::kInt, {B, n}, "parent_idx");
@@ -254,8 +259,7 @@ PyObject *prune(PyObject *, PyObject *const *o, Py_ssize_t nargs) {
   const double tau = PyFloat_AsDouble(o[2]);
   if (tau == -1.0 && PyErr_Occurred()) throw python_error();
   const long budget = number(o[3]);
-  const int scored = PyObject_IsTrue(o[4]);
-  if (scored < 0) throw python_error();
+  const bool scored = truth(o[4]);
   const void *pp = device_pointer(parent, at::kInt, {B, n}, "parent");
   const void *lp = pointer(o[1], at::kFloat, {B, n}, "logp");
   const auto ints = parent.options().dtype(at::kInt);

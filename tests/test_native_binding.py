@@ -56,6 +56,27 @@ def test_host_tensors_and_non_tensors_are_refused(name):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("part", range(6), ids=["k", "u", "alpha", "parent", "path", "len"])
+def test_incomplete_pending_is_refused(part):
+    calls = _calls("cuda")
+    call, a = calls["verify"]
+    f, path, ln = a["factors"], a["parent_idx"].clone(), torch.zeros(2, dtype=torch.int32, device="cuda")
+    prev = [f.k.clone(), f.u.clone(), f.alpha.clone(), f.parent.clone(), path, ln]
+    before = [x.clone() for x in (a["state"], a["out"], f.u)]
+    prev[part] = None  # a missing part of a pending round is an error, not a call without one
+    with pytest.raises((TypeError, AttributeError)):
+        call(pending=(B.Factors(*prev[:4]), prev[4], prev[5]))
+    if part in (0, 3, 4, 5):  # the convolution's pending rows hold x, parent, path and len
+        call, a2 = calls["conv_verify"]
+        conv = {0: a2["x"].clone(), 3: path.clone(), 4: path, 5: ln}
+        conv[part] = None
+        with pytest.raises((TypeError, AttributeError)):
+            call(pending=tuple(conv.values()))
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(before, (a["state"], a["out"], f.u)))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("name", ["verify", "commit", "conv_verify", "conv_commit", "prune"])
 def test_wrong_shapes_types_and_layouts_are_refused(name):
     call, tensors = _calls("cuda")[name]
