@@ -310,6 +310,11 @@ def sla_conv_verify(conv_state, x, weight, parent_idx, y, *, bias=None, pending:
 def sla_conv_commit(conv_state, x, parent_idx, path, length, *, kernel_size=None, status=None):
     """Enqueue an immediate conv-state commit of the accepted paths (see
     sla_conv_commit).  conv_state [B][K-1][D] fp32 (None when K = 1)."""
+    if kernel_size is not None and not isinstance(kernel_size, int):
+        whole = int(kernel_size)
+        if conv_state is not None and whole != kernel_size:
+            raise ValueError("kernel_size must be a whole number, got %s" % kernel_size)
+        kernel_size = whole
     code = (_nat or native()).conv_commit(conv_state, x, parent_idx, path, length, kernel_size, status)
     _check(code, "sla_conv_commit")
 

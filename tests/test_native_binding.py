@@ -4,6 +4,7 @@ is launched, on the CPU and for tensors on the GPU, and a call runs on the
 calling thread's current stream."""
 import threading
 
+import numpy as np
 import pytest
 import torch
 
@@ -74,6 +75,30 @@ def test_incomplete_pending_is_refused(part):
             call(pending=tuple(conv.values()))
     torch.cuda.synchronize()
     assert all(torch.equal(x, y) for x, y in zip(before, (a["state"], a["out"], f.u)))
+
+
+def test_kernel_size_takes_any_whole_number():
+    """Whole numbers of any type pass on to the tensor checks, others are refused."""
+    call, a = _calls("cpu")["conv_commit"]
+    for k in (4, 4.0, np.int64(4), np.float32(4.0)):
+        with pytest.raises(ValueError, match="must live on the GPU"):
+            call(kernel_size=k)
+    with pytest.raises(ValueError, match="whole number"):
+        call(kernel_size=4.5)
+
+
+@pytest.mark.gpu
+def test_kernel_size_as_a_float_commits():
+    call, a = _calls("cuda")["conv_commit"]
+    a["x"].normal_()
+    path = (a["parent_idx"] + 1).contiguous()  # the chain's own nodes, root first
+    got = []
+    for k in (None, 4, 4.0):
+        a["conv_state"].fill_(1.0)
+        call(kernel_size=k, path=path, length=torch.full((2,), 2, dtype=torch.int32, device="cuda"))
+        got.append(a["conv_state"].clone())
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+    assert torch.equal(got[0][:, 1:], a["x"][:, :2])
 
 
 @pytest.mark.gpu
