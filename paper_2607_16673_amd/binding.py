@@ -234,6 +234,14 @@ class Factors:
                        torch.empty(gate_shape(batch, n, heads, d_k, family), dtype=torch.float32, device=device),
                        torch.empty(batch, n, dtype=torch.int32, device=device))
 
+    def c(self, dtype, B, n, H, dk, dv, family="gdn") -> SlaFactors:
+        """The store as the C ABI's sla_factors, for callers that use ctypes themselves."""
+        torch = _torch()
+        return SlaFactors(_dev(self.k, dtype, (B, n, H, dk), "factors.k"),
+                          _dev(self.u, torch.float32, (B, n, H, dv), "factors.u"),
+                          _dev(self.alpha, torch.float32, gate_shape(B, n, H, dk, family), "factors.alpha"),
+                          _dev(self.parent, torch.int32, (B, n), "factors.parent"))
+
 
 def _check(code, what):
     if code != SLA_OK:

@@ -77,6 +77,21 @@ def test_incomplete_pending_is_refused(part):
     assert all(torch.equal(x, y) for x, y in zip(before, (a["state"], a["out"], f.u)))
 
 
+@pytest.mark.gpu
+def test_factors_as_a_c_structure():
+    f = B.Factors.empty(2, 4, 3, 64, 32, torch.bfloat16)
+    c = f.c(torch.bfloat16, 2, 4, 3, 64, 32)
+    assert (c.k, c.u, c.alpha, c.parent) == tuple(t.data_ptr() for t in (f.k, f.u, f.alpha, f.parent))
+    with pytest.raises(ValueError, match="factors.k"):
+        f.c(torch.bfloat16, 2, 5, 3, 64, 32)
+
+
+def test_factors_as_a_c_structure_takes_gpu_tensors_only():
+    f = B.Factors.empty(2, 4, 3, 64, 32, torch.bfloat16, device="cpu")
+    with pytest.raises(ValueError, match="factors.k must live on the GPU"):
+        f.c(torch.bfloat16, 2, 4, 3, 64, 32)
+
+
 def test_kernel_size_takes_any_whole_number():
     """Whole numbers of any type pass on to the tensor checks, others are refused."""
     call, a = _calls("cpu")["conv_commit"]
