@@ -5,7 +5,8 @@ Every HIP translation unit is compiled by hipcc for gfx950 only, with packed
 fp32 instructions disabled (the library relies on ordinary fp32 VALU and
 matrix-core arithmetic), then linked into one shared library.  The Python
 binding's marshalling module (_native) is host code linked against it and
-against torch.
+against torch; the library needs neither torch nor Python and is installed
+first.
 """
 import importlib.util
 import os
@@ -53,10 +54,17 @@ def _compile(unit, verbose: bool) -> str:
     return obj
 
 
+def _torch_dir() -> str:
+    """torch's place without importing it."""
+    spec = importlib.util.find_spec("torch")
+    if spec is None or not spec.origin:
+        raise RuntimeError("torch is not installed: the Python binding's native module cannot be built")
+    return os.path.dirname(spec.origin)
+
+
 def _compile_native(verbose: bool) -> str:
     """The marshalling module's object file (host code only)."""
-    # torch's place without importing it
-    torch = os.path.dirname(importlib.util.find_spec("torch").origin)
+    torch = _torch_dir()
     obj = os.path.join(BUILD, "torch_binding.o")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            "-I" + INCLUDE, "-isystem" + os.path.join(torch, "include"), "-isystem/opt/rocm/include",
@@ -64,14 +72,17 @@ def _compile_native(verbose: bool) -> str:
            "-c", os.path.join(CSRC, "torch_binding.cpp"), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
-    r = subprocess.run(cmd, capture_output=True, text=True)
+    try:
+        r = subprocess.run(cmd, capture_output=True, text=True)
+    except FileNotFoundError as e:
+        raise RuntimeError("g++ is not installed: the Python binding's native module cannot be built") from e
     if r.returncode != 0:
         raise RuntimeError("g++ failed for torch_binding.cpp:\n" + r.stdout + r.stderr)
     return obj
 
 
 def _link_native(obj: str, verbose: bool) -> None:
-    torch = os.path.join(os.path.dirname(importlib.util.find_spec("torch").origin), "lib")
+    torch = os.path.join(_torch_dir(), "lib")
     cmd = ["g++", "-shared", "-fPIC", "-o", NATIVE + ".tmp", obj, "-L" + HERE, "-l:libsla.so", "-L" + torch, "-ltorch_python",
            "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + torch]
     if verbose:
@@ -85,13 +96,13 @@ def build(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
         native = ex.submit(_compile_native, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
-        native = native.result()
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", LIB + ".tmp"] + objs
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(LIB + ".tmp", LIB)
-    _link_native(native, verbose)
+    # the C library stands on its own: a module that cannot be built leaves it in place
+    _link_native(native.result(), verbose)
     return LIB
 
 
