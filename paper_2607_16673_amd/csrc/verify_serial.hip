@@ -401,11 +401,18 @@ hipError_t launch_hybrid_dk(const VerifyArgs &a, hipStream_t s) {
     const bool vg = a.family == SLA_FAMILY_GLA;
     const size_t one = serial_stage_bytes(a.n, DK, vg) + hybrid_extra_bytes(a.n);
     if (one > kMaxLds) return hipErrorInvalidConfiguration;
-    // one stage per CU: two tiles share it, four once pairs would fill the CUs
-    // more than once (8 heads, d_v 256, fp32, one, two and four tiles: 64 nodes
-    // at batch 8 261, --, 104 us; 48 nodes at batch 4 (512 tiles) 106, 64, -- us)
+    // One stage per CU: once the 16-column tiles outnumber the CUs, two share a
+    // stage, four once pairs would fill the CUs more than once (8 heads, d_v
+    // 256, fp32, one, two and four tiles: 64 nodes at batch 8 261, --, 104 us;
+    // 48 nodes at batch 4 (512 tiles) 106, 64, -- us).  Below that each tile
+    // has a CU to itself and sharing only takes waves from it (48 nodes at
+    // batch 1, one and two tiles: trees 45.9 and 48.2 us, stars, whose leaves
+    // then run on one wave, 40.4 and 59.1; 40 nodes with per-key gates 52.5
+    // and 71.0).  The shared forms spill 14 registers with scalar gates, 78 to
+    // 80 with per-key gates (two register copies of a 256-row slice at 512
+    // threads).
     const size_t slices = (size_t)a.B * a.H * (a.dv / kCols), cus = device_cus();
-    if (2 * one > kMaxLds) {
+    if (2 * one > kMaxLds && slices > cus) {
       auto fits = [&](int sl) { return shared_stage_bytes(a.n, DK, vg, sl) + hybrid_extra_bytes(a.n) <= kMaxLds; };
       if (slices > 2 * cus && a.dv / kCols > 2 && fits(4)) return launch_hybrid_w<DK, T, 2, 4>(a, s);
       if (a.dv / kCols > 1 && fits(2)) return launch_hybrid_w<DK, T, 4, 2>(a, s);

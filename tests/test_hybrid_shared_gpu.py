@@ -15,10 +15,13 @@ from test_hybrid_gpu import _dev, _problem, _two_rounds
 
 pytestmark = pytest.mark.gpu
 
-# batch, heads, d_v, nodes, dtype, family: 16-column tiles on each side of one and two per CU
+# batch, heads, d_v, nodes, dtype, family: 16-column tiles on each side of one per CU (no sharing
+# up to there) and of two
 CASES = [(4, 4, 256, 64, inputs.F32, "gdn"), (5, 4, 256, 64, inputs.F32, "deltanet"),
          (20, 4, 48, 33, inputs.F32, "decay"), (33, 4, 80, 40, inputs.F32, "gdn"), (40, 8, 32, 48, inputs.F32, "gdn"),
-         (17, 2, 256, 48, inputs.BF16, "gla"), (40, 1, 208, 50, inputs.F32, "gla"), (16, 8, 112, 41, inputs.BF16, "gla")]
+         (17, 2, 256, 48, inputs.BF16, "gla"), (40, 1, 208, 50, inputs.F32, "gla"), (16, 8, 112, 41, inputs.BF16, "gla"),
+         # pairs of tiles: an odd tile count, per-key gates just above one tile per CU
+         (30, 4, 48, 33, inputs.F32, "decay"), (10, 2, 256, 48, inputs.BF16, "gla"), (15, 1, 288, 50, inputs.F32, "gla")]
 
 
 @pytest.mark.parametrize("i", range(len(CASES)), ids=["B%d_H%d_dv%d_n%d_%s_%s" % c for c in CASES])
