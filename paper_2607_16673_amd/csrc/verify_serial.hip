@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kWave) void verify_serial_kernel(VerifyArgs a) {
 // ---------------------------------------------------------------- hybrid
 constexpr int kMaxLevels = 8;  // light edges on a root path <= log2(64) = 6
 
-// LDS beyond the stage: light leaf children [n] (64-bit masks), per-level
+// LDS beyond the stage: light leaf children [n] (64-bit masks, shared stages), per-level
 // chain-head lists [kMaxLevels][n], per-level counts, the error code and the
 // deepest level.  (The heavy-child keys and children lie in the stage.)
 __host__ __device__ inline size_t hybrid_extra_bytes(int n) {
@@ -238,12 +238,18 @@ __global__ __launch_bounds__(W * SL * kWave) void verify_hybrid_kernel(VerifyArg
       // with few waves per tile, light leaf children are verified from the
       // state their parent's chain has on chip (a node's outputs need its
       // parent's state only), not as chains of their own that rebuild it
-      const bool leaf_child = SL > 1 && head && topo.parent >= 0 && topo.n_children == 0;
-      const uint64_t leaf_children = __ballot(leaf_child);
-      uint64_t mine = 0;
-      for (int i = 0; i < n; ++i)
-        mine |= ((leaf_children >> i) & 1ull) && __builtin_amdgcn_readlane(topo.parent, i) == lane ? 1ull << i : 0ull;
-      const uint64_t starts = heads & ~leaf_children;  // the chains
+      uint64_t starts = heads;  // the chains
+      bool start = head;
+      if constexpr (SL > 1) {
+        const bool leaf_child = head && topo.parent >= 0 && topo.n_children == 0;
+        const uint64_t leaf_children = __ballot(leaf_child);
+        uint64_t mine = 0;
+        for (int i = 0; i < n; ++i)
+          mine |= ((leaf_children >> i) & 1ull) && __builtin_amdgcn_readlane(topo.parent, i) == lane ? 1ull << i : 0ull;
+        if (live) leaves[lane] = mine;
+        starts &= ~leaf_children;
+        start = start && !leaf_child;
+      }
       // level: chain starts strictly above this node's chain head
       const int lvl = live ? __popcll(topo.anc & heads) - 1 : 0;
       const int hd = live ? 63 - __builtin_clzll(topo.anc & heads) : -1;  // this node's chain head
@@ -263,12 +269,10 @@ __global__ __launch_bounds__(W * SL * kWave) void verify_hybrid_kernel(VerifyArg
         const int li = __builtin_amdgcn_readlane(lvl, i);
         cnt += ((starts >> i) & 1ull) && li == lane;
       }
-      const bool start = head && !leaf_child;
       int deepest = start ? lvl : 0;
       for (int o = 1; o < kWave; o <<= 1) deepest = max(deepest, __shfl_xor(deepest, o));
       if (live) {
         heavy[lane] = hv;
-        leaves[lane] = mine;
         s.ancs[lane] = topo.anc;
       }
       // (heavy-light: a chain start at least halves the subtree, so a 64-node
@@ -315,10 +319,12 @@ __global__ __launch_bounds__(W * SL * kWave) void verify_hybrid_kernel(VerifyArg
         const float u = node_step<DK, R, VG>(a, s, Hc, j, b, h, c, g, row0, col, delta);
         const int nx = heavy[j];
         if (nx >= 0) advance<DK, R, VG>(s, Hc, j, row0, u);
-        uint64_t lm = readlane_u64(leaves[j], 0);  // wave-uniform; none without a heavy child
-        while (lm) {
-          node_step<DK, R, VG>(a, s, Hc, __builtin_ctzll(lm), b, h, c, g, row0, col, delta);
-          lm &= lm - 1;
+        if constexpr (SL > 1) {
+          uint64_t lm = readlane_u64(leaves[j], 0);  // wave-uniform; none without a heavy child
+          while (lm) {
+            node_step<DK, R, VG>(a, s, Hc, __builtin_ctzll(lm), b, h, c, g, row0, col, delta);
+            lm &= lm - 1;
+          }
         }
         j = nx;
       }
