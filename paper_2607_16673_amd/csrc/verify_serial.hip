@@ -424,8 +424,9 @@ hipError_t launch_hybrid_dk(const VerifyArgs &a, hipStream_t s) {
       if (a.dv / kCols > 1 && fits(2)) return launch_hybrid_w<DK, T, 4, 2>(a, s);
     }
     return launch_hybrid_w<DK, T, 4>(a, s);
+  } else {
+    return a.n <= 16 ? launch_hybrid_w<DK, T, 4>(a, s) : launch_hybrid_w<DK, T, 8>(a, s);
   }
-  return a.n <= 16 ? launch_hybrid_w<DK, T, 4>(a, s) : launch_hybrid_w<DK, T, 8>(a, s);
 }
 
 template <typename T>
