@@ -188,14 +188,6 @@ __global__ __launch_bounds__(kWave) void topology_kernel(TopologyArgs a) {
   a.n_children[r + lane] = t.n_children;
 }
 
-int device_cus() {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-    return 256;
-  return cus;
-}
-
 template <typename T, int DK>
 hipError_t launch_commit_dk(const CommitArgs &a, hipStream_t s) {
   auto kern = a.gate_vec ? commit_kernel<T, DK, true> : commit_kernel<T, DK, false>;

@@ -265,14 +265,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 5))
   }
 }
 
-int device_cus() {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-    return 256;
-  return cus;
-}
-
 template <typename T, int DK>
 hipError_t launch_dk(const VerifyArgs &a, hipStream_t s) {
   auto kern = a.family == SLA_FAMILY_GLA ? decode_kernel<T, DK, true> : decode_kernel<T, DK, false>;

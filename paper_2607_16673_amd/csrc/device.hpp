@@ -241,4 +241,13 @@ __device__ inline int check_path(const int32_t *__restrict__ parent_row, int n,
   return wave_any(bad) ? SLA_ERR_PATH : SLA_OK;
 }
 
+// Compute units of the current device (host).
+inline int device_cus() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+    return 256;
+  return cus;
+}
+
 }  // namespace sla

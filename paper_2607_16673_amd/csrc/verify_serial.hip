@@ -393,14 +393,6 @@ hipError_t launch_hybrid_w(const VerifyArgs &a, hipStream_t s) {
   return launch_with_lds(verify_hybrid_kernel<DK, T, false, W, SL>, grid, block, lds, s, a);
 }
 
-int device_cus() {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-    return 256;
-  return cus;
-}
-
 template <int DK, typename T>
 hipError_t launch_hybrid_dk(const VerifyArgs &a, hipStream_t s) {
   if constexpr (DK == 256) {

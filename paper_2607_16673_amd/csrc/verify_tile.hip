@@ -1131,15 +1131,6 @@ void verify_tile_kernel(VerifyArgs a) {
   if constexpr (TPW == 2) step(1, hfb, hfa);
 }
 
-
-int device_cus() {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-    return 256;
-  return cus;
-}
-
 // Rounds of workgroups from which a launch is kModeLate.
 constexpr int kLateRounds = 4;
 
