@@ -476,9 +476,18 @@ hipError_t launch_verify(const ConvArgs &a, hipStream_t s) {
   const size_t groups = (size_t)a.B * ((a.D + CL * kCpl - 1) / (CL * kCpl));
   // The waves split the draft's nodes: eight for drafts of more than 32 nodes
   // (64-node trees at batch 256: 117 us; 143 us with four that all read rows),
-  // else four, and a fifth where each then has several rows left (batch 64, 16
-  // nodes: 10.9 -> 10.5 us; with four nodes 11.4 -> 14.2 us).
-  const int most = a.n > 32 ? kConvWaves : (CL == kWave && a.n > 8 ? 5 : 4), need = NR / RW;
+  // else four; five up to three workgroups per CU, which then still all run at
+  // once (bf16, 6144 channels, whole chunks, four and five waves: batch 64,
+  // three per CU, 8 and 16 nodes 10.3 and 9.5, 13.4 and 12.4 us; batch 85,
+  // four per CU, 8 nodes 11.7 and 13.9; batch 128, six, 16.4 and 19.3, 16
+  // nodes 21.6 and 24.5; batch 256, 16 nodes 34.5 and 41.1 us).  Narrow
+  // chunks of more than 32 nodes take eight up to one workgroup per CU (batch
+  // 4, 64 nodes, four, five and eight: 7.3, 7.3, 6.2 us), then as many as fit
+  // (batch 16, 64 nodes: 10.9, 10.5, 13.2 us).
+  const size_t cus = device_cus();
+  const int fit = groups <= 3 * cus ? 5 : 4;
+  const int most = CL == kWave ? (a.n > 32 ? kConvWaves : fit) : (a.n > 32 ? (groups <= cus ? kConvWaves : fit) : 4);
+  const int need = NR / RW;
   const int waves = need < 2 ? 2 : (need < most ? need : most);
   const size_t lds = ((size_t)kPieces<XT> * NR * CL + (size_t)K1 * 2 * CL + (size_t)(2 * K * CL + kWave - 1) / kWave * kWave) * 16 + 16;
   auto kern = conv_verify_kernel<XT, K, CL>;

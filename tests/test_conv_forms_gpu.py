@@ -17,9 +17,11 @@ from test_conv_gpu import check_outputs, random_draft, run_verify, to_np
 
 pytestmark = pytest.mark.gpu
 
-# batch, channels, nodes: batch x ceil(channels / 512) on each side of 32 and 256
+# batch, channels, nodes: batch x ceil(channels / 512) on each side of 32 and 256; narrow chunks on each
+# side of one and three workgroups per CU above 32 nodes; whole chunks on each side of three
 CASES = [(31, 504, 2), (32, 504, 3), (16, 1032, 33), (8, 2056, 64), (128, 1016, 5), (129, 520, 9), (257, 136, 8),
-         (128, 1024, 17), (86, 1544, 16), (300, 8, 64)]
+         (128, 1024, 17), (86, 1544, 16), (300, 8, 64),
+         (40, 1032, 33), (85, 1032, 40), (300, 520, 6), (800, 16, 7)]
 
 
 @pytest.mark.parametrize("i", range(len(CASES)), ids=["B%d_D%d_n%d" % c for c in CASES])
