@@ -102,6 +102,17 @@ constexpr int kKindDelta = 0, kKindGates = 1;
 // Template parameters: a run-time choice of the store policy or of the place
 // of the state reads costs most of what it gains.
 constexpr int kModePart = 0, kModeRound = 1, kModeLate = 2;
+// fp32 activations with per-key gates take the late place in every mode for 32
+// node rows and at d_k 256: the staged rows and gates then leave their registers
+// before the state needs any (138 -> 228 VGPRs with the reads first at d_k 256,
+// 32 nodes), and the scores hide the reads (reads first and late: 24 sequences,
+// 8 heads, d_v 128, d_k 256, 16 nodes 29.3 and 25.4 us; d_k 128, 32 nodes 24.9
+// and 20.0; batch 1, 12 heads, d_v 144, 23 nodes 10.7 and 10.6).  Not where it
+// gains nothing on the whole: 64 node rows, 16 at d_k 64 and 128; nor with
+// eight column waves, which read the state behind the scores there (d_k = d_v =
+// 256, 32 nodes 43.1 and 45.7).
+template <int DK, int NP, int CW, int KIND, bool F32>
+constexpr bool kLateAlways = KIND == kKindGates && F32 && CW < 8 && NP <= 32 && (NP == 32 || DK == 256);
 
 // F32: fp32 activations.  q, k, v and the pending keys are staged and read
 // as fp32, and every contraction runs on v_mfma_f32_16x16x4_f32 with exact
@@ -216,7 +227,7 @@ void verify_tile_kernel(VerifyArgs a) {
   constexpr bool DELTA = KIND == kKindDelta;
   constexpr bool GV = KIND == kKindGates;
   const bool nodelta = !DELTA || a.family == SLA_FAMILY_DECAY;  // R = V
-  constexpr bool kLate = MODE == kModeLate;
+  constexpr bool kLate = MODE == kModeLate || kLateAlways<DK, NP, CW, KIND, F32>;
   constexpr bool WT = MODE == kModeRound;       // committed rows written through at device scope
   constexpr int kColWaves = CW;                 // waves 0 .. CW-1 own state columns
   constexpr int kSetup = kWaves<CW> == CW ? 0 : CW;  // the setup wave
@@ -1144,7 +1155,7 @@ hipError_t launch_np(const VerifyArgs &a, hipStream_t s) {
     using Kernel = void (*)(VerifyArgs);
     const Kernel part = verify_tile_kernel<DK, NP, CW, TPW, KIND, F32, kModePart>;
     const Kernel round = verify_tile_kernel<DK, NP, CW, TPW, KIND, F32, kModeRound>;
-    const Kernel late = verify_tile_kernel<DK, NP, CW, TPW, KIND, F32, kModeLate>;
+    const Kernel late = verify_tile_kernel<DK, NP, CW, TPW, KIND, F32, kLateAlways<DK, NP, CW, KIND, F32> ? kModePart : kModeLate>;
     auto allow_lds = [](Kernel k) {
       if (lds <= kDefaultLds) return hipSuccess;
       return hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -25,7 +25,10 @@ CASES = [(1, 2, 128, 128, 64, 48, "gdn", inputs.BF16), (2, 2, 64, 80, 9, 17, "de
          (3, 1, 256, 48, 33, 32, "gdn", inputs.BF16), (1, 3, 128, 256, 17, 64, "gdn", inputs.BF16),
          (2, 1, 128, 64, 40, 33, "gla", inputs.BF16), (130, 8, 128, 128, 12, 16, "gdn", inputs.BF16),
          (70, 16, 128, 128, 24, 31, "gdn", inputs.BF16), (300, 16, 64, 64, 16, 15, "decay", inputs.F32),
-         (66, 16, 128, 144, 10, 23, "gla", inputs.F32), (140, 16, 128, 256, 20, 40, "gdn", inputs.BF16)]
+         (66, 16, 128, 144, 10, 23, "gla", inputs.F32), (140, 16, 128, 256, 20, 40, "gdn", inputs.BF16),
+         # fp32 with per-key gates, the state read behind the first barrier: d_k 256, and 32 node rows
+         (24, 8, 256, 128, 12, 16, "gla", inputs.F32), (12, 6, 128, 96, 9, 23, "gla", inputs.F32),
+         (30, 8, 64, 320, 20, 32, "gla", inputs.F32)]
 
 
 def _parents(r, Bn, n):
