@@ -19,8 +19,8 @@
 // inverse of those blocks.  Only the committed state is read.
 //
 // One workgroup = one (batch b, head h) unit's V-tile of CW x 16 columns
-// (CW = 4 or 8), or TPW = 2 consecutive such tiles, with CW + 1 wavefronts
-// (CW = 4) or CW (CW = 8, where column wave 0 also takes the setup work):
+// (CW = 3, 4 or 8), or TPW = 2 consecutive such tiles, with CW + 1 wavefronts
+// (CW = 3 or 4) or CW (CW = 8, where column wave 0 also takes the setup work):
 //   waves 0 .. CW-1 own 16 state columns each.  They bring [Q; K] (a share
 //              each, through registers into LDS), then, held back briefly, the
 //              state tile (in the B-fragment order of
@@ -241,7 +241,7 @@ void verify_tile_kernel(VerifyArgs a) {
   float *tb = reinterpret_cast<float *>(lds + L::oT);         // -Lk blocks; diagonal ones become N = T - I
   float *ab = reinterpret_cast<float *>(lds + L::oAt);        // Attn blocks
   AT *s_pk = reinterpret_cast<AT *>(lds + L::oPk);            // [kPMax][DK]
-  float *s_pu = reinterpret_cast<float *>(lds + L::oPu);      // [kPMax][64]
+  float *s_pu = reinterpret_cast<float *>(lds + L::oPu);      // [TPW][kPMax][kPuPitch]
   uint4 *xl = reinterpret_cast<uint4 *>(lds + L::oXL);        // GLA: low halves of Q~
   float *s_g = reinterpret_cast<float *>(lds + L::oG);        // GLA: [NP][DK] gates
   float *s_pg = reinterpret_cast<float *>(lds + L::oPg);      // GLA: [kPMax][DK] pending gates
@@ -654,7 +654,7 @@ void verify_tile_kernel(VerifyArgs a) {
         const int j = (it0 + l) >> 4, d0 = ((it0 + l) & 15) * E;
         const bool first = (l & 15) == 0;
         float qc[E];
-        load_row(j, d0, qc);  // padding rows hold node 0's query
+        load_row(j, d0, qc);  // padding rows are zero
         uint64_t rest = j < n ? s_anc[j] : 0ull;
         // every lane takes all maxd steps, so the DPP rows stay whole
 #pragma unroll 1
@@ -1178,12 +1178,35 @@ hipError_t launch_np(const VerifyArgs &a, hipStream_t s) {
   }
 }
 
-// One V-tile per workgroup: 48 columns instead of 64 where the same number of
-// tiles then covers d_v with fewer waves (d_v 48, 80, 96, 144).
+// One V-tile per workgroup: 48 columns instead of 64 where as many tiles then
+// cover d_v with fewer waves (d_v 16 to 48, 80, 96, 144) and that lets more
+// workgroups share a CU.  Geometric means of three waves against four over
+// these d_v, 12 heads, batch 1 to 256:
+//   scalar gates  d_k 64 0.95, 0.97, 0.95 at 8, 23 and 48 nodes, d_k 128 0.96,
+//                 0.95, 0.98, d_k 256 0.93, 0.94, at most 4% longer (batch 40,
+//                 d_k 256, d_v 80, 8 and 23 nodes: 36.2 -> 29.5, 46.6 -> 35.5 us);
+//                 not for 33 to 64 nodes at d_k 256, where one stage fills a CU
+//                 anyway (1.01, up to 1.05);
+//   per-key gates the scores are spread over the column waves, so fewer waves
+//                 cost where the launch does not fill the CUs: 1.02 to 1.13
+//                 below two tiles per CU, 1.00 to 1.05 from two to three (d_k
+//                 256, and 128 in fp32, up to 16 nodes) or to four.  Above that
+//                 0.90 to 1.00 for the forms of kThreeWaves, 1.01 to 1.05 for
+//                 the others (no more workgroups per CU, or registers spilled
+//                 to fit them), 1.04 to 1.07 for 33 to 64 nodes.
+template <int DK, int NP, int KIND, bool F32>
+constexpr bool kThreeWaves =
+    KIND == kKindDelta ? DK < 256 || NP < 64
+                       : (NP == 16 ? DK != 128 || F32 : NP == 32 && (DK == 64 || (DK == 128 && !F32)));
+
 template <int DK, int NP, int KIND, bool F32>
 hipError_t launch_single(const VerifyArgs &a, hipStream_t s) {
-  const int waves = a.dv / kWaveCols;
-  if (waves % 4 != 0 && (waves + 2) / 3 == (waves + 3) / 4) return launch_np<DK, NP, 3, 1, KIND, F32>(a, s);
+  if constexpr (kThreeWaves<DK, NP, KIND, F32>) {
+    const int waves = a.dv / kWaveCols, tiles = (waves + 3) / 4;
+    if (waves % 4 != 0 && (waves + 2) / 3 == tiles &&
+        (KIND == kKindDelta || (size_t)a.B * a.H * tiles > (size_t)(NP == 16 && DK > 64 ? 3 : 4) * device_cus()))
+      return launch_np<DK, NP, 3, 1, KIND, F32>(a, s);
+  }
   return launch_np<DK, NP, 4, 1, KIND, F32>(a, s);
 }
 

@@ -28,7 +28,12 @@ CASES = [(1, 2, 128, 128, 64, 48, "gdn", inputs.BF16), (2, 2, 64, 80, 9, 17, "de
          (66, 16, 128, 144, 10, 23, "gla", inputs.F32), (140, 16, 128, 256, 20, 40, "gdn", inputs.BF16),
          # fp32 with per-key gates, the state read behind the first barrier: d_k 256, and 32 node rows
          (24, 8, 256, 128, 12, 16, "gla", inputs.F32), (12, 6, 128, 96, 9, 23, "gla", inputs.F32),
-         (30, 8, 64, 320, 20, 32, "gla", inputs.F32)]
+         (30, 8, 64, 320, 20, 32, "gla", inputs.F32),
+         # tiles of 48 columns: scalar gates (not at d_k 256 above 32 nodes), per-key gates above three or four tiles per CU
+         (3, 2, 256, 80, 9, 24, "gdn", inputs.F32), (2, 2, 256, 80, 9, 40, "gdn", inputs.BF16),
+         (129, 8, 64, 48, 10, 30, "gla", inputs.F32), (49, 8, 256, 96, 10, 15, "gla", inputs.BF16),
+         (43, 8, 128, 144, 12, 17, "gla", inputs.BF16), (42, 8, 128, 144, 12, 17, "gla", inputs.BF16),
+         (129, 8, 128, 16, 10, 9, "gla", inputs.F32)]
 
 
 def _parents(r, Bn, n):
