@@ -33,7 +33,10 @@ CASES = [(1, 2, 128, 128, 64, 48, "gdn", inputs.BF16), (2, 2, 64, 80, 9, 17, "de
          (3, 2, 256, 80, 9, 24, "gdn", inputs.F32), (2, 2, 256, 80, 9, 40, "gdn", inputs.BF16),
          (129, 8, 64, 48, 10, 30, "gla", inputs.F32), (49, 8, 256, 96, 10, 15, "gla", inputs.BF16),
          (43, 8, 128, 144, 12, 17, "gla", inputs.BF16), (42, 8, 128, 144, 12, 17, "gla", inputs.BF16),
-         (129, 8, 128, 16, 10, 9, "gla", inputs.F32)]
+         (129, 8, 128, 16, 10, 9, "gla", inputs.F32),
+         # pairs of 64-column tiles where one stage fills a CU and d_v holds no whole 128-column tile
+         (18, 8, 128, 80, 20, 48, "gla", inputs.BF16), (17, 8, 128, 96, 12, 40, "gdn", inputs.F32),
+         (17, 8, 256, 112, 20, 24, "gla", inputs.F32), (17, 8, 256, 80, 20, 48, "gdn", inputs.BF16)]
 
 
 def _parents(r, Bn, n):
