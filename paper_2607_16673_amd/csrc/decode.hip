@@ -33,8 +33,15 @@ constexpr int kThreads = 256;
 constexpr int kCols = 64;   // state columns per workgroup
 constexpr int kStage = 8;   // path records staged in LDS; longer paths read the rest directly
 
-template <typename T, int DK, bool VG>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 5))) void decode_kernel(VerifyArgs a) {
+// MOST: the most waves per SIMD.  More streams than these take the state's lines
+// out of order (16 heads, one pending node, scalar gates in bf16: d_k 128, five
+// and four waves: batch 64, d_v 128 28.9 and 27.8 us, batch 256, d_v 256 184.6
+// and 180.8; d_k 256, batch 256, d_v 256, four, three and two: 399, 366, 354 us;
+// d_k 64, batch 256, d_v 256, eight and six: 98.5 and 96.4).  But a launch of at
+// most eight workgroups per CU runs at once with eight (d_k 64, batch 64, d_v
+// 128, six and eight: bf16 16.3 and 15.4 us, fp32 16.5 and 15.6).
+template <typename T, int DK, bool VG, int MOST>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, MOST))) void decode_kernel(VerifyArgs a) {
   constexpr int R = DK / 16;  // rows per thread
   __shared__ int s_err, s_len;
   __shared__ float s_alpha[kStage];
@@ -265,9 +272,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 5))
   }
 }
 
-template <typename T, int DK>
-hipError_t launch_dk(const VerifyArgs &a, hipStream_t s) {
-  auto kern = a.family == SLA_FAMILY_GLA ? decode_kernel<T, DK, true> : decode_kernel<T, DK, false>;
+template <typename T, int DK, int MOST>
+hipError_t launch_most(const VerifyArgs &a, hipStream_t s) {
+  auto kern = a.family == SLA_FAMILY_GLA ? decode_kernel<T, DK, true, MOST> : decode_kernel<T, DK, false, MOST>;
   const int nslab = (a.dv + kCols - 1) / kCols;
   const size_t groups = (size_t)a.B * a.H * nslab;
   VerifyArgs b = a;
@@ -275,6 +282,16 @@ hipError_t launch_dk(const VerifyArgs &a, hipStream_t s) {
   b.xcd_group = b.write_through && nslab >= kXcdGroupMin;
   hipLaunchKernelGGL(kern, dim3((unsigned)xcd_grid((size_t)a.B * a.H, nslab, b.xcd_group)), dim3(kThreads), 0, s, b);
   return hipGetLastError();
+}
+
+template <typename T, int DK>
+hipError_t launch_dk(const VerifyArgs &a, hipStream_t s) {
+  if constexpr (DK == 64) {
+    if ((size_t)a.B * a.H * ((a.dv + kCols - 1) / kCols) <= (size_t)8 * device_cus()) return launch_most<T, DK, 8>(a, s);
+    return launch_most<T, DK, 6>(a, s);
+  } else {
+    return launch_most<T, DK, DK == 128 ? 4 : 2>(a, s);
+  }
 }
 
 template <typename T>

@@ -120,6 +120,39 @@ def test_one_node_fused_round(fam, dt, dk, dv):
     assert es <= tol and eo <= tol and er <= tol
 
 
+@pytest.mark.parametrize("fam,dt,Bn", [("gdn", inputs.BF16, 128), ("gdn", inputs.BF16, 129), ("gla", inputs.F32, 131)])
+def test_one_node_on_each_side_of_eight_workgroups_per_cu(fam, dt, Bn):
+    """d_k 64: launches that fit at once and larger ones take forms of their
+    own; a sequence alone gives the bits it gives in the batch."""
+    H, dk, dv, npend = 16, 64, 48, 3
+    c_prev = inputs.Config("wp", 960, Bn, H, dk, dv, npend, True, npend, 1, dt, 1)
+    c_node = inputs.Config("wn", 961, Bn, H, dk, dv, 1, True, 1, 1, dt, 1)
+    prev, cur = Round(c_prev, fam, 0), Round(c_node, fam, 1)
+    plen = np.arange(Bn, dtype=np.int32) % (npend + 1)
+    ppath = np.where(np.arange(npend) < plen[:, None], np.arange(npend), -1).astype(np.int32)
+    S0 = inputs.draw_state(c_prev, 0)
+    f_prev = _factors(c_prev, fam)
+    _verify(c_prev, fam, prev, _dev(S0), torch.empty(Bn, npend, H, dv, device="cuda"), f_prev)
+    state, out, f = _dev(S0), torch.empty(Bn, 1, H, dv, device="cuda"), _factors(c_node, fam)
+    path, length = _dev(ppath), _dev(plen)
+    _verify(c_node, fam, cur, state, out, f, pending=(f_prev, path, length))
+    torch.cuda.synchronize()
+    for b in (0, 2, Bn - 1):
+        s = slice(b, b + 1)
+        cut = lambda x: None if x is None else x[s].contiguous()
+        alone, o1 = _dev(S0[s]), torch.empty(1, 1, H, dv, device="cuda")
+        f1 = B.Factors(*(torch.empty_like(cut(x)) for x in (f.k, f.u, f.alpha, f.parent)))
+        B.sla_verify(alone, cut(cur.q), cut(cur.k), cut(cur.v), cut(cur.a), cut(cur.b), cut(cur.parent), o1, f1,
+                     pending=(B.Factors(*(cut(x) for x in (f_prev.k, f_prev.u, f_prev.alpha, f_prev.parent))),
+                              cut(path), cut(length)), topology="chain", family=fam)
+        assert torch.equal(alone, state[s]) and torch.equal(o1, out[s]) and torch.equal(f1.u, f.u[s])
+        refS, _ = oracle.commit(S0[s], prev.rnd.k32[0][s], prev.rnd.v32[0][s], prev.alpha[s],
+                                None if prev.beta is None else prev.beta[s], prev.rnd.parent[s], ppath[s], plen[s], family=fam)
+        ref, _ = oracle.verify(refS, cur.rnd.q32[0][s], cur.rnd.k32[0][s], cur.rnd.v32[0][s], cur.alpha[s],
+                               None if cur.beta is None else cur.beta[s], cur.rnd.parent[s], family=fam)
+        assert rel_err(alone.cpu().numpy(), refS) <= TOL[dt] and rel_err(o1.cpu().numpy(), ref) <= TOL[dt]
+
+
 def test_one_node_refuses_bad_parent_and_path():
     """A node that is not a child of the committed state, or a pending path
     that is not a root path, is reported per sequence and leaves its state
