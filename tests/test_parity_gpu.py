@@ -126,10 +126,10 @@ def test_fused_round_matches_oracle_and_standalone_bitwise(name, route):
     _fused_round_check(inputs.config(name), route)
 
 
-# Larger trees over several V-tiles: two tiles per workgroup (d_v 80 with a
-# partial second tile, d_v 128), one per workgroup (d_v 192, three tiles);
-# root paths within and beyond the depth that solves T in registers; and
-# small trees at batch sizes where they pair V-tiles too.
+# Larger trees over several V-tiles (d_v 80 with a partial second tile, d_v 128,
+# 192, 256), one tile per workgroup in launches as small as these (the wider
+# forms are in test_tile_forms_gpu.py); root paths within and across the 16-row
+# blocks; and small trees at batch sizes where they pair V-tiles.
 LARGE = [
     inputs.Config("tree48_dv80", 95, 3, 3, 128, 80, 48, False, 6, 4, inputs.BF16, 1),
     inputs.Config("tree48_dv128", 96, 2, 4, 128, 128, 48, False, 12, 3, inputs.BF16, 1),

@@ -36,7 +36,17 @@ CASES = [(1, 2, 128, 128, 64, 48, "gdn", inputs.BF16), (2, 2, 64, 80, 9, 17, "de
          (129, 8, 128, 16, 10, 9, "gla", inputs.F32),
          # pairs of 64-column tiles where one stage fills a CU and d_v holds no whole 128-column tile
          (18, 8, 128, 80, 20, 48, "gla", inputs.BF16), (17, 8, 128, 96, 12, 40, "gdn", inputs.F32),
-         (17, 8, 256, 112, 20, 24, "gla", inputs.F32), (17, 8, 256, 80, 20, 48, "gdn", inputs.BF16)]
+         (17, 8, 256, 112, 20, 24, "gla", inputs.F32), (17, 8, 256, 80, 20, 48, "gdn", inputs.BF16),
+         # eight column waves, just above one or two tiles per CU: one tile of 128 columns, pairs of them; with
+         # per-key gates; in less than a round of workgroups
+         (17, 8, 256, 128, 20, 48, "gdn", inputs.BF16), (17, 8, 128, 128, 20, 40, "gdn", inputs.F32),
+         (9, 8, 256, 384, 20, 24, "gla", inputs.F32), (9, 8, 128, 384, 9, 33, "gla", inputs.F32),
+         (9, 8, 256, 256, 20, 48, "gdn", inputs.BF16), (9, 8, 256, 256, 20, 24, "gdn", inputs.F32),
+         (9, 8, 256, 256, 20, 24, "gla", inputs.BF16), (9, 8, 128, 256, 20, 40, "gla", inputs.BF16),
+         (20, 8, 128, 256, 20, 40, "gdn", inputs.BF16), (17, 8, 64, 256, 20, 40, "deltanet", inputs.F32),
+         (17, 8, 64, 256, 20, 33, "gla", inputs.BF16),
+         # pairs of 64-column tiles, 33 to 64 nodes, two stages per CU
+         (33, 8, 128, 128, 20, 40, "gdn", inputs.BF16), (33, 8, 64, 80, 20, 48, "decay", inputs.F32)]
 
 
 def _parents(r, Bn, n):
