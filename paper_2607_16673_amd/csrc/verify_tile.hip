@@ -737,60 +737,60 @@ void verify_tile_kernel(VerifyArgs a) {
   auto grams = [&]() {
     if constexpr (!GV) {
       f32x4 gacc[GT];
-    int tc = 0;
+      int tc = 0;
 #pragma unroll
-    for (int mr = 0; mr < MT; ++mr)
+      for (int mr = 0; mr < MT; ++mr)
 #pragma unroll
-      for (int na = 0; na <= mr % NT; ++na, ++tc) {
-        if (tc % kColWaves != w || (mr % NT) * 16 >= n || (!DELTA && mr >= NT)) continue;
-        f32x4 g = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int na = 0; na <= mr % NT; ++na, ++tc) {
+          if (tc % kColWaves != w || (mr % NT) * 16 >= n || (!DELTA && mr >= NT)) continue;
+          f32x4 g = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          if constexpr (F32) {
-            float av[8], bv[8];
-            frag8(mr * 16 + lc, ks, av);
-            frag8(NP + na * 16 + lc, ks, bv);
+          for (int ks = 0; ks < KS; ++ks) {
+            if constexpr (F32) {
+              float av[8], bv[8];
+              frag8(mr * 16 + lc, ks, av);
+              frag8(NP + na * 16 + lc, ks, bv);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) g = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], bv[e], g, 0, 0, 0);
-          } else {
-            const bf16x8 af = *reinterpret_cast<const bf16x8 *>(xs + xchunk<CH>(mr * 16 + lc, ks * 4 + lg));
-            const bf16x8 bf = *reinterpret_cast<const bf16x8 *>(xs + xchunk<CH>(NP + na * 16 + lc, ks * 4 + lg));
-            g = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf, g, 0, 0, 0);
+              for (int e = 0; e < 8; ++e) g = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], bv[e], g, 0, 0, 0);
+            } else {
+              const bf16x8 af = *reinterpret_cast<const bf16x8 *>(xs + xchunk<CH>(mr * 16 + lc, ks * 4 + lg));
+              const bf16x8 bf = *reinterpret_cast<const bf16x8 *>(xs + xchunk<CH>(NP + na * 16 + lc, ks * 4 + lg));
+              g = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf, g, 0, 0, 0);
+            }
+          }
+          gacc[tc / kColWaves] = g;
+        }
+      tc = 0;
+#pragma unroll
+      for (int mr = 0; mr < MT; ++mr)
+#pragma unroll
+        for (int na = 0; na <= mr % NT; ++na, ++tc) {
+          if (tc % kColWaves != w || (mr % NT) * 16 >= n || (!DELTA && mr >= NT)) continue;
+          // every LDS read of the tile's metadata is issued before its first
+          // write, so they share one round trip
+          const int bj = mr % NT;
+          const int an = na * 16 + lc;
+          const int jb = bj * 16 + 4 * lg;
+          uint32_t anc[4];  // the half of row j's ancestor mask that holds column an
+          float dj[4], be4[4];  // dj: decay ratio D_{j,an}, parked where the entry goes
+          float *const db = (mr < NT ? ab : tb) + ((bj * (bj + 1)) / 2 + na) * (16 * kBP) + 4 * lg * kBP + lc;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            anc[q] = reinterpret_cast<const uint32_t *>(s_anc)[2 * (jb + q) + (na >> 1)];
+            dj[q] = db[q * kBP];
+            be4[q] = mr >= NT ? s_be[jb + q] : 0.f;
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int j = jb + q;
+            // every entry is written: zero unless an is an ancestor of j (rows
+            // past the last node hold stale LDS words: masked by j < n; the
+            // diagonal of Lk is not read)
+            const bool on = j < n && an <= j && !(mr >= NT && an == j) && ((anc[q] >> (an & 31)) & 1u);
+            const float dg = dj[q] * gacc[tc / kColWaves][q];
+            db[q * kBP] = on ? (mr < NT ? dg : -(be4[q] * dg)) : 0.f;
           }
         }
-        gacc[tc / kColWaves] = g;
-      }
-    tc = 0;
-#pragma unroll
-    for (int mr = 0; mr < MT; ++mr)
-#pragma unroll
-      for (int na = 0; na <= mr % NT; ++na, ++tc) {
-        if (tc % kColWaves != w || (mr % NT) * 16 >= n || (!DELTA && mr >= NT)) continue;
-        // every LDS read of the tile's metadata is issued before its first
-        // write, so they share one round trip
-        const int bj = mr % NT;
-        const int an = na * 16 + lc;
-        const int jb = bj * 16 + 4 * lg;
-        uint32_t anc[4];  // the half of row j's ancestor mask that holds column an
-        float dj[4], be4[4];  // dj: decay ratio D_{j,an}, parked where the entry goes
-        float *const db = (mr < NT ? ab : tb) + ((bj * (bj + 1)) / 2 + na) * (16 * kBP) + 4 * lg * kBP + lc;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          anc[q] = reinterpret_cast<const uint32_t *>(s_anc)[2 * (jb + q) + (na >> 1)];
-          dj[q] = db[q * kBP];
-          be4[q] = mr >= NT ? s_be[jb + q] : 0.f;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int j = jb + q;
-          // every entry is written: zero unless an is an ancestor of j (rows
-          // past the last node hold stale LDS words: masked by j < n; the
-          // diagonal of Lk is not read)
-          const bool on = j < n && an <= j && !(mr >= NT && an == j) && ((anc[q] >> (an & 31)) & 1u);
-          const float dg = dj[q] * gacc[tc / kColWaves][q];
-          db[q * kBP] = on ? (mr < NT ? dg : -(be4[q] * dg)) : 0.f;
-        }
-      }
     }
   };
 

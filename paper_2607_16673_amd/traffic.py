@@ -46,7 +46,7 @@ COPY_TAG = "mul"  # the elementwise multiply of run_copy (not the fill before it
 _COMMON = ["device.hpp", "kernels.hpp", "api.cpp"]
 SOURCES = {
     "verify_tile_kernel": ["verify_tile.hip", "verify_tile_dispatch.cpp"] + _COMMON,
-    "verify_serial_kernel": ["verify_serial.hip"] + _COMMON,
+    "verify_serial_kernel": ["verify_serial.hip", "serial_stage.hpp"] + _COMMON,
     "decode_kernel": ["decode.hip"] + _COMMON,
     "commit_kernel": ["commit.hip"] + _COMMON,
     "conv_verify_kernel": ["conv.hip", "device.hpp", "layer_ops.hpp", "api.cpp"],
