@@ -20,8 +20,8 @@
 // wave shuffles.  After one barrier every node's window is read from LDS by
 // ancestor index: K fused multiply-adds per channel, SiLU, one 16-byte store
 // per lane.  (With wave 0 reading rows as well, its path check waited for
-// them: one sequence of 32 nodes took 8.9 us, now 4.1; 64-node trees at batch
-// 256 137 us, now 117.)
+// them: one sequence of 32 nodes, 6144 channels, took 8.9 us, now 4.1; 64-node
+// trees at batch 256, 8192 channels 145 us, now 133.)
 // A 1-node draft (the decode step) takes a single wave that reads its row
 // and the conv state straight into registers (conv_node_kernel).
 // The bound is HBM: the draft rows and outputs stream once, the conv state
@@ -475,8 +475,7 @@ hipError_t launch_verify(const ConvArgs &a, hipStream_t s) {
   const int NR = (a.n + RW - 1) / RW * RW, K1 = K > 1 ? K - 1 : 1;
   const size_t groups = (size_t)a.B * ((a.D + CL * kCpl - 1) / (CL * kCpl));
   // The waves split the draft's nodes: eight for drafts of more than 32 nodes
-  // (64-node trees at batch 256: 117 us; 143 us with four that all read rows),
-  // else four; five up to three workgroups per CU, which then still all run at
+  // (batch 256, 64 nodes, 6144 channels: 101 us; 114 us with four), else four; five up to three workgroups per CU, which then still all run at
   // once (bf16, 6144 channels, whole chunks, four and five waves: batch 64,
   // three per CU, 8 and 16 nodes 10.3 and 9.5, 13.4 and 12.4 us; batch 85,
   // four per CU, 8 nodes 11.7 and 13.9; batch 128, six, 16.4 and 19.3, 16

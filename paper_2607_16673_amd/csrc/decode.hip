@@ -33,14 +33,19 @@ constexpr int kThreads = 256;
 constexpr int kCols = 64;   // state columns per workgroup
 constexpr int kStage = 8;   // path records staged in LDS; longer paths read the rest directly
 
-// MOST: the most waves per SIMD.  More streams than these take the state's lines
-// out of order (16 heads, one pending node, scalar gates in bf16: d_k 128, five
-// and four waves: batch 64, d_v 128 28.9 and 27.8 us, batch 256, d_v 256 184.6
-// and 180.8; d_k 256, batch 256, d_v 256, four, three and two: 399, 366, 354 us;
-// d_k 64, batch 256, d_v 256, eight and six: 98.5 and 96.4).  But a launch of at
-// most eight workgroups per CU runs at once with eight (d_k 64, batch 64, d_v
-// 128, six and eight: bf16 16.3 and 15.4 us, fp32 16.5 and 15.6).
-template <typename T, int DK, bool VG, int MOST>
+// PEND: a pending path is applied; without one the call only reads the state,
+// and runs straight from the reads to the sums (the records' code in the way, not
+// taken, cost 4 to 10%: 16 heads, batch 256, d_k 64, d_v 256 49.8 -> 52.9 us).
+// MOST: the most waves per SIMD.  Reading and writing, more streams than these
+// take the state's lines out of order (16 heads, one pending node, scalar gates
+// in bf16: d_k 128, five and four waves: batch 64, d_v 128 28.9 and 27.8 us,
+// batch 256, d_v 256 184.6 and 180.8; d_k 256, batch 256, d_v 256, four, three
+// and two: 399, 366, 354 us; d_k 64, batch 256, d_v 256, eight and six: 98.5 and
+// 96.4).  But a launch of at most eight workgroups per CU runs at once with
+// eight (d_k 64, batch 64, d_v 128, six and eight: bf16 16.3 and 15.4 us, fp32
+// 16.5 and 15.6), and reads alone want every wave (no pending path, d_k 256,
+// batch 256, d_v 256, four and two: 182 and 203 us).
+template <typename T, int DK, bool VG, bool PEND, int MOST>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, MOST))) void decode_kernel(VerifyArgs a) {
   constexpr int R = DK / 16;  // rows per thread
   __shared__ int s_err, s_len;
@@ -64,13 +69,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, MOS
   const bool delta = a.family == SLA_FAMILY_GDN || a.family == SLA_FAMILY_DELTANET;
 
   // wave 0: the draft's parent and the pending path, ahead of the slab reads
-  const int pn = a.has_pending ? a.pend.n : 1;
+  const int pn = PEND ? a.pend.n : 1;
   const size_t rowp = (size_t)b * pn;
   int len = 0, pnode = -1, ppar = -2, p0 = 0;
   float pal = 0.f;
   if (w == 0) {
     p0 = a.parent[b];
-    if (a.has_pending) {
+    if (PEND) {
       len = a.pend.len[b];
       pnode = l < pn ? a.pend.path[rowp + l] : -1;
       ppar = l < pn ? a.pend.parent[rowp + l] : -2;
@@ -118,7 +123,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, MOS
     int err = wave_any(p0 != -1) ? SLA_ERR_TOPOLOGY : SLA_OK;
     const bool inrange = pnode >= 0 && pnode < pn;
     const int nodec = inrange ? pnode : 0;
-    if (err == SLA_OK && a.has_pending) {
+    if (err == SLA_OK && PEND) {
       int prev = __shfl_up(pnode, 1);
       if (l == 0) prev = -1;
       const int pp = __shfl(ppar, nodec);
@@ -128,11 +133,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, MOS
     const float pa = __shfl(pal, nodec);
     if (l == 0) {
       s_err = err;
-      s_len = a.has_pending ? len : 0;
+      s_len = PEND ? len : 0;
     }
     if (l < kStage) s_alpha[l] = pa;
     if (h == 0 && slab == 0 && l == 0 && a.status) a.status[b] = err;
-    if (a.has_pending) {
+    if (PEND) {
       // records of the first steps (indices clamped into the store): key
       // rows, gate rows and this slab's corrected values, straight into LDS
       const T *pk = static_cast<const T *>(a.pend.k);
@@ -166,7 +171,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, MOS
   len = s_len;
 
   // delayed update: the accepted records, root first, then the write-back
-  if (len > 0) {
+  if (PEND && len > 0) {
     const int cs = (tid % 16) * 4;
     for (int t = 0; t < len && t < kStage; ++t) {  // step by step: one read of u for all rows
       const float4 u = *reinterpret_cast<const float4 *>(&s_u[t][cs]);
@@ -272,9 +277,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, MOS
   }
 }
 
-template <typename T, int DK, int MOST>
-hipError_t launch_most(const VerifyArgs &a, hipStream_t s) {
-  auto kern = a.family == SLA_FAMILY_GLA ? decode_kernel<T, DK, true, MOST> : decode_kernel<T, DK, false, MOST>;
+template <typename T, int DK, bool PEND, int MOST>
+hipError_t launch_form(const VerifyArgs &a, hipStream_t s) {
+  auto kern = a.family == SLA_FAMILY_GLA ? decode_kernel<T, DK, true, PEND, MOST> : decode_kernel<T, DK, false, PEND, MOST>;
   const int nslab = (a.dv + kCols - 1) / kCols;
   const size_t groups = (size_t)a.B * a.H * nslab;
   VerifyArgs b = a;
@@ -286,11 +291,12 @@ hipError_t launch_most(const VerifyArgs &a, hipStream_t s) {
 
 template <typename T, int DK>
 hipError_t launch_dk(const VerifyArgs &a, hipStream_t s) {
+  if (!a.has_pending) return launch_form<T, DK, false, 8>(a, s);
   if constexpr (DK == 64) {
-    if ((size_t)a.B * a.H * ((a.dv + kCols - 1) / kCols) <= (size_t)8 * device_cus()) return launch_most<T, DK, 8>(a, s);
-    return launch_most<T, DK, 6>(a, s);
+    if ((size_t)a.B * a.H * ((a.dv + kCols - 1) / kCols) <= (size_t)8 * device_cus()) return launch_form<T, DK, true, 8>(a, s);
+    return launch_form<T, DK, true, 6>(a, s);
   } else {
-    return launch_most<T, DK, DK == 128 ? 4 : 2>(a, s);
+    return launch_form<T, DK, true, DK == 128 ? 4 : 2>(a, s);
   }
 }
 
