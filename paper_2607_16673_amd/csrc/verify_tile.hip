@@ -199,12 +199,14 @@ constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) 
 // Waves per SIMD the register allocation is held to: 6 (80 VGPRs) where the
 // tile state, accumulators and LDS allow a fourth resident workgroup per CU;
 // 4 (128 VGPRs) for the eight-wave form where its LDS lets two workgroups fit
-// a CU; else whatever the allocation needs.
+// a CU; 5 (96) for 64 node rows in fp32 at d_k 64 (116 otherwise: 16 heads, batch
+// 64, d_v 128, 48 nodes 67 us, 58 held); else whatever the allocation needs.
 constexpr size_t kMaxLds = 160 * 1024;
 constexpr size_t kDefaultLds = 64 * 1024;
 template <int DK, int NP, int CW, int TPW, int KIND, bool F32>
 constexpr int kMinWaves =
-    F32 ? 1 : ((DK <= 128 && NP <= 16) ? 6 : (CW == 8 && 2 * Layout<DK, NP, CW, TPW, KIND, F32>::kBytes <= kMaxLds ? 4 : 1));
+    F32 ? (KIND == kKindDelta && DK == 64 && NP == 64 && CW == 4 ? 5 : 1)
+        : ((DK <= 128 && NP <= 16) ? 6 : (CW == 8 && 2 * Layout<DK, NP, CW, TPW, KIND, F32>::kBytes <= kMaxLds ? 4 : 1));
 
 // KIND: the family's form (see Layout).  Without the delta rule Lk = 0, so
 // T = I and U = R = V: no P_k, no Lk, no T.
@@ -233,6 +235,7 @@ void verify_tile_kernel(VerifyArgs a) {
   constexpr int kSetup = kWaves<CW> == CW ? 0 : CW;  // the setup wave
   constexpr int kTileCols = L::kTileCols;       // state columns per workgroup
   constexpr int KS = L::KS, NT = L::NT, MT = L::MT, CH = L::CH;
+  constexpr bool kUnitT = F32 && NT == 1;                   // T with its diagonal (see U = T R)
   constexpr int NGT = NT * (NT + 1);                        // Gram tiles (both halves)
   constexpr int GT = (NGT + kColWaves - 1) / kColWaves;     // Gram tiles per column wave
 
@@ -836,7 +839,7 @@ void verify_tile_kernel(VerifyArgs a) {
   plen = s_misc[1];
 
   if (DELTA && w == kSetup) {
-    // ---- the diagonal blocks of T = (I + Lk)^-1, less the identity, in place
+    // ---- the diagonal blocks of T = (I + Lk)^-1, less the identity (kUnitT: with it), in place
     //      (the off-diagonal blocks stay -Lk: U = T R is a substitution block
     //      row by block row).  Lane (nb, c) solves column c of block nb by
     //      forward substitution in registers; the cost does not depend on the
@@ -862,7 +865,7 @@ void verify_tile_kernel(VerifyArgs a) {
         x[j] = sum;
       }
 #pragma unroll
-      for (int j = 0; j < 16; ++j) db[j * kBP + c] = j == c ? 0.f : x[j];
+      for (int j = 0; j < 16; ++j) db[j * kBP + c] = j == c ? (kUnitT ? 1.f : 0.f) : x[j];
     }
   }
 
@@ -1082,16 +1085,28 @@ void verify_tile_kernel(VerifyArgs a) {
       for (int mt = 0; mt < NT; ++mt) {
         uacc[mt] = rreg[mt];
         if constexpr (DELTA && F32) {
+          // the corrections are summed by themselves and R enters once, at the
+          // end: in the accumulators from the start it rounds every product at
+          // its own size (64-node chains, d_k 64: U's error from fp64 6.0e-8,
+          // then 1.5e-7; 16-node chains 6.5e-8 and 8.3e-8).  A single block
+          // takes R through the diagonal of T instead: no register holds R to
+          // the end (the paired form would need 82, and a wave per SIMD less).
           // A operand i: column 16 ks + 4 lg + i of row 16 mt + lc, B operand i: U[16 ks + 4 lg + i][lc]
+          f32x4 cor = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int ks = 0; ks < mt; ++ks) {
             const f32x4 lv = blockrow(tb, mt, ks);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) uacc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(lv[i], uacc[ks][i], uacc[mt], 0, 0, 0);
+            for (int i = 0; i < 4; ++i) cor = __builtin_amdgcn_mfma_f32_16x16x4f32(lv[i], uacc[ks][i], cor, 0, 0, 0);
           }
-          const f32x4 nv = blockrow(tb, mt, mt), x = uacc[mt];
+          const f32x4 nv = blockrow(tb, mt, mt);
+          f32x4 x;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) uacc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(nv[i], x[i], uacc[mt], 0, 0, 0);
+          for (int i = 0; i < 4; ++i) x[i] = mt == 0 ? rreg[0][i] : rreg[mt][i] + cor[i];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) cor = __builtin_amdgcn_mfma_f32_16x16x4f32(nv[i], x[i], cor, 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) uacc[mt][i] = kUnitT ? cor[i] : rreg[mt][i] + cor[i];
         } else if constexpr (DELTA) {
           s16x4 ah, al2, xh, xl2;
 #pragma unroll

@@ -119,3 +119,30 @@ def test_deep_paths_and_regimes(i):
         alone, ob, gb = dev(S0[s]), torch.empty(1, n1, H, dv, device="cuda"), fac(n1, 1)
         verify(alone, 1, gb, ob, pend=(fb, dev(path[s]), dev(ln[s])), s=s)
         assert torch.equal(alone, fused[s]) and torch.equal(ob, out1[s]) and torch.equal(gb.u, f1.u[s])
+
+
+@pytest.mark.parametrize("dk,n", [(64, 64), (128, 48), (256, 32)])
+def test_fp32_corrected_values_hold_fp32(dk, n):
+    """Corrected values of long fp32 chains against the step's definition in
+    fp64: R = beta (v - gamma P) and the sum of R with its corrections (far
+    smaller than R) round once each, at most 2^-24 of the value, so the
+    2-norm stays within 2 x 2^-24 (summed product by product on top of R it
+    was 1.1e-7 to 1.5e-7)."""
+    Bn, H, dv = 3, 2, 64
+    cfg = inputs.Config("tp", 790 + n, Bn, H, dk, dv, n, True, n, 1, inputs.F32, 1)
+    rd = inputs.draw_round(cfg, 0, layers=[0])
+    S0 = inputs.draw_state(cfg, 0)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    f = B.Factors.empty(Bn, n, H, dk, dv, torch.float32)
+    B.sla_verify(dev(S0), *(act_tensor(x[0], inputs.F32) for x in (rd.q, rd.k, rd.v)), dev(rd.alpha[0]), dev(rd.beta[0]),
+                 dev(rd.parent), torch.empty(Bn, n, H, dv, device="cuda"), f, topology="chain")
+    S = torch.from_numpy(S0).double()  # [B][H][dk][dv]
+    k, v, al, be = (torch.from_numpy(np.ascontiguousarray(x[0])).double() for x in (rd.k32, rd.v32, rd.alpha, rd.beta))
+    want = torch.empty(Bn, n, H, dv, dtype=torch.float64)
+    for j in range(n):
+        S = S * al[:, j, :, None, None]
+        want[:, j] = be[:, j, :, None] * (v[:, j] - (S * k[:, j, :, :, None]).sum(2))
+        S = S + k[:, j, :, :, None] * want[:, j, :, None, :]
+    err = float((f.u.cpu().double() - want).norm() / want.norm())
+    print("dk %d n %d: corrected values %.2e from fp64" % (dk, n, err), flush=True)
+    assert err <= 2 * 2.0 ** -24
